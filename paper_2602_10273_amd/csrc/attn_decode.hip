@@ -7,13 +7,13 @@
 // gfx950 design.  The kernel is a stream over K and V (each read once, 16-byte loads); the two contractions run on the
 // matrix cores so that the vector ALUs only see the softmax.  One workgroup of 2 waves per (row, KV head, split of the
 // positions); a wave walks tiles of 16 positions:
-//   scores   S^T[pos, head] = K_tile[pos, dim] Q^T[dim, head]: 16x16x16 bf16 MFMA, A = the K tile exactly as loaded
+//   scores   S^T[pos, head] = K_tile[pos, dim] Q^T[dim, head]: 16x16x32 bf16 MFMA, A = the K tile exactly as loaded
 //            (lane = (pos, 8-dim slice)), B = the group's query heads (padded to 16) preloaded in registers;
 //   softmax  online, base 2, one running maximum per head; the result lane (head, 4 positions) is already the A
 //            operand layout of the second contraction;
-//   output   O[head, dim] += P[head, pos] V_tile[pos, dim]: the V tile goes through LDS (rows padded to 272 bytes, so
-//            the 2-byte transposed reads are conflict-free) to become the B operand; P is fed as bf16 high + low parts
-//            (two MFMAs), which keeps the result within ~1e-5 of fp64.
+//   output   O[head, dim] += P[head, pos] V_tile[pos, dim]: the V tile goes through LDS as rows and comes back through
+//            transposed 8-byte reads (ds_read_b64_tr_b16) as the B operand; rows are padded by 32 bytes so that a read meets
+//            every bank once; P is fed as bf16 high + low parts (two 16x16x16 MFMAs), which keeps the result within ~1e-5 of fp64.
 // Waves are merged through LDS; with more than one split a second small kernel merges the splits.
 #include <math.h>
 
@@ -23,11 +23,19 @@ namespace psmc {
 
 namespace {
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef bf16x4 __attribute__((address_space(3)))* lds_bf16x4_ptr;
 typedef unsigned int vec16 __attribute__((ext_vector_type(4)));
 
 constexpr int kAttnWaves = 2;             // waves per workgroup: small workgroups overlap each other's start-up and merge
 constexpr int kTile = 16;                 // positions per MFMA tile
+// Tiles held in registers: one in use, kDepth - 1 on their way.  The stream is bound by how many bytes a wave has in flight
+// (one wave per SIMD where there are 512 workgroups): 8 KiB a tile at D = 128, 1.4 us from request to arrival under load.
+// The former two-buffer loop branched round its loads and so waited for all of them at every tile.  Measured for 128 rows x
+// 4 KV heads x 2031 positions: 91.2 us (5.9 TB/s) before, 85.4 with 3 tiles, 81.3 with 4; 64 rows x 8 heads x 1337 paged
+// positions: 63.6 before, 51.3 with 3 (6.9 TB/s), 54.1 with 4, whose 368 registers leave one wave per SIMD.
+constexpr int kDepth = 3;
 constexpr int kHeadsPad = 16;             // query heads of a group, padded to the MFMA width
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -40,9 +48,6 @@ struct AttnSrc {
     int P, M;                   // positions per page, pages per row
     int H, S;                   // KV heads, positions per row (dense)
 };
-
-__device__ __forceinline__ bf16x4 lo4(const vec16 v) { bf16x4 r; __builtin_memcpy(&r, &v, 8); return r; }
-__device__ __forceinline__ bf16x4 hi4(const vec16 v) { bf16x4 r; __builtin_memcpy(&r, (const char*)&v + 8, 8); return r; }
 
 // p = hi + lo with hi, lo representable in bf16 (hi by truncation, lo rounded to nearest even); returns the bit patterns
 __device__ __forceinline__ void split_bf16(float p, unsigned& hi, unsigned& lo)
@@ -72,7 +77,7 @@ __global__ __launch_bounds__(kAttnWaves* kWave) void attn_decode_kernel(
     constexpr int NKL = D / 32;                 // 16-byte K loads per lane and tile
     constexpr int NDB = D / 16;                 // 16-dim blocks of the output
     constexpr int NVL = D / 32;                 // 16-byte V loads per lane and tile (16 positions x D x 2 bytes / 64 lanes / 16)
-    constexpr int kRowBytes = D * 2 + 16;       // padded LDS row of a V tile
+    constexpr int kRowBytes = D * 2 + 32;       // padded LDS row of a V tile: 8 rows x 32 bytes of a transposed read meet 64 banks once
     constexpr int kPiecesPerRow = D / 8;        // 16-byte pieces per position
     constexpr int kPosBytes = D * 2;
     __shared__ __attribute__((aligned(16))) char sh_v[kAttnWaves][kTile * kRowBytes];
@@ -80,7 +85,8 @@ __global__ __launch_bounds__(kAttnWaves* kWave) void attn_decode_kernel(
     __shared__ float sh_m[kAttnWaves][kHeadsPad], sh_l[kAttnWaves][kHeadsPad];
     __shared__ float sh_o[kAttnWaves][kHeadsPad][D];           // each wave's scaled output, summed when written out
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // scalar: tile numbers and tile addresses stay scalar
     const int c = lane & 15, j = lane >> 4;
     const int split = blockIdx.x % n_splits;
     const int head = (blockIdx.x / n_splits) % src.H;
@@ -100,7 +106,7 @@ __global__ __launch_bounds__(kAttnWaves* kWave) void attn_decode_kernel(
     }
 
     // the group's query heads as B operands: lane (head c, j) holds dims 32u + 8j .. + 7 of head c
-    bf16x4 qb[2 * NKL];
+    bf16x8 qb[NKL];
     {
         const bool have = c < G;
         const uint16_t* qp = q + ((int64_t)row * Hq + (int64_t)head * G + (have ? c : 0)) * D;
@@ -108,8 +114,7 @@ __global__ __launch_bounds__(kAttnWaves* kWave) void attn_decode_kernel(
         for (int u = 0; u < NKL; ++u) {
             vec16 v = *(const vec16*)(qp + 32 * u + 8 * j);
             if (!have) v = vec16{0u, 0u, 0u, 0u};
-            qb[2 * u] = lo4(v);
-            qb[2 * u + 1] = hi4(v);
+            __builtin_memcpy(&qb[u], &v, 16);
         }
     }
 
@@ -123,8 +128,7 @@ __global__ __launch_bounds__(kAttnWaves* kWave) void attn_decode_kernel(
 #pragma unroll
     for (int t = 0; t < NDB; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // Where the positions of this (row, KV head) live (see the MODE enumeration).  Page numbers are read one tile
-    // ahead of the loads that need them, so the dependent load does not stall the stream.
+    // Where the positions of this (row, KV head) live (see the MODE enumeration).
     const int P = src.P;
     const int32_t* table_row = MODE == kDense ? nullptr : src.table + (int64_t)row * src.M;
     const int64_t page_stride = (int64_t)src.H * P * kPosBytes;
@@ -138,69 +142,67 @@ __global__ __launch_bounds__(kAttnWaves* kWave) void attn_decode_kernel(
         kbase = src.kA + (int64_t)head * P * kPosBytes;
         vbase = src.vA + (int64_t)head * P * kPosBytes;
     }
-    // lane-constant parts of the addresses inside a tile
-    const int k_lane_off = c * kPosBytes + 16 * j;                              // position c of the tile, 16-byte piece j of a 64-byte run
-    int v_lane_pos[NVL], v_lane_off[NVL];
-#pragma unroll
-    for (int u = 0; u < NVL; ++u) {
-        const int piece = u * kWave + lane;
-        v_lane_pos[u] = piece / kPiecesPerRow;
-        v_lane_off[u] = (piece % kPiecesPerRow) * 16;
-    }
+    // This wave's tiles are tile_begin + wave + kAttnWaves * i, i < n_mine.
+    const int first = tile_begin + wave;
+    const int n_mine = first < tile_end ? (tile_end - first + kAttnWaves - 1) / kAttnWaves : 0;
+    // The pages of a tile (kPagedAligned: one scalar; kPagedAny: one per lane and 16-byte piece), read one tile ahead of
+    // the loads that need them.
     struct TilePages { int k; int v[NVL]; };
-    auto lookup = [&](int tile, TilePages& tp) {
-        const int p0 = tile * kTile;
-        if (MODE == kPagedAligned) {
+    auto lookup = [&](int i, TilePages& tp) __attribute__((always_inline)) {
+        const int p0 = (first + kAttnWaves * (i < n_mine ? i : n_mine - 1)) * kTile;
+        if constexpr (MODE == kPagedAligned) {
             tp.k = table_row[p0 / P];                                           // one page for the whole tile
-        } else if (MODE == kPagedAny) {
+        } else if constexpr (MODE == kPagedAny) {
             tp.k = table_row[min(p0 + c, len - 1) / P];
 #pragma unroll
-            for (int u = 0; u < NVL; ++u) tp.v[u] = table_row[min(p0 + v_lane_pos[u], len - 1) / P];
+            for (int u = 0; u < NVL; ++u) tp.v[u] = table_row[min(p0 + (u * kWave + lane) / kPiecesPerRow, len - 1) / P];
         }
     };
-    // Positions past the end repeat the last valid one (their weights are masked to zero).
-    auto load_tile = [&](int tile, const TilePages& tp, vec16 (&kd)[NKL], vec16 (&vd)[NVL]) {
-        const int p0 = tile * kTile;
-        const bool whole = p0 + kTile <= len;                                   // uniform: no clamping needed
-        const char* kp; const char* vp[NVL];
-        if (MODE == kDense) {
-            const char* kt = kbase + (int64_t)p0 * kPosBytes;
-            const char* vt = vbase + (int64_t)p0 * kPosBytes;
-            kp = kt + (whole ? k_lane_off : min(c, len - 1 - p0) * kPosBytes + 16 * j);
+    // Loads this wave's tile i.  Every call issues the same loads, without a branch round them, so that the compiler can
+    // count them: at the merge of such a branch the wait for an older tile would become a wait for everything in flight.
+    // Positions past `len` repeat the last valid one (their weights are masked to zero); a tile past the wave's last
+    // (i >= n_mine) reads one position over and over.
+    auto load_tile = [&](int i, const TilePages& tp, vec16 (&kd)[NKL], vec16 (&vd)[NVL]) __attribute__((always_inline)) {
+        const bool real = i < n_mine;
+        const int p0 = (first + kAttnWaves * (real ? i : 0)) * kTile;
+        if constexpr (MODE != kPagedAny) {
+            const int last = real ? min(len - 1 - p0, kTile - 1) : 0;           // last position of the tile that is read
+            int64_t at = (int64_t)p0 * kPosBytes;
+            if constexpr (MODE == kPagedAligned) at = tp.k * page_stride + (int64_t)(p0 % P) * kPosBytes;
+            const char* kt = kbase + at;
+            const char* vt = vbase + at;
+            const unsigned k_off = min(c, last) * kPosBytes + 16 * j;
 #pragma unroll
-            for (int u = 0; u < NVL; ++u)
-                vp[u] = vt + (whole ? v_lane_pos[u] : min(v_lane_pos[u], len - 1 - p0)) * kPosBytes + v_lane_off[u];
-        } else if (MODE == kPagedAligned) {
-            const int64_t in_page = (int64_t)(p0 % P) * kPosBytes;
-            const char* kt = kbase + tp.k * page_stride + in_page;
-            const char* vt = vbase + tp.k * page_stride + in_page;
-            kp = kt + (whole ? k_lane_off : min(c, len - 1 - p0) * kPosBytes + 16 * j);
-#pragma unroll
-            for (int u = 0; u < NVL; ++u)
-                vp[u] = vt + (whole ? v_lane_pos[u] : min(v_lane_pos[u], len - 1 - p0)) * kPosBytes + v_lane_off[u];
-        } else {
-            const int kpos = min(p0 + c, len - 1);
-            kp = kbase + tp.k * page_stride + (int64_t)(kpos % P) * kPosBytes + 16 * j;
+            for (int u = 0; u < NKL; ++u) kd[u] = stream_load(kt + (k_off + 64 * u));        // dims 32u + 8j .. + 7 of position c
 #pragma unroll
             for (int u = 0; u < NVL; ++u) {
-                const int vpos = min(p0 + v_lane_pos[u], len - 1);
-                vp[u] = vbase + tp.v[u] * page_stride + (int64_t)(vpos % P) * kPosBytes + v_lane_off[u];
+                const unsigned pos = u * (kWave / kPiecesPerRow) + lane / kPiecesPerRow;
+                vd[u] = stream_load(vt + (min(pos, (unsigned)last) * kPosBytes + lane % kPiecesPerRow * 16));
+            }
+        } else {
+            const int kpos = min(p0 + c, len - 1);
+            const char* kp = kbase + tp.k * page_stride + (int64_t)(kpos % P) * kPosBytes + 16 * j;
+#pragma unroll
+            for (int u = 0; u < NKL; ++u) kd[u] = stream_load(kp + 64 * u);
+#pragma unroll
+            for (int u = 0; u < NVL; ++u) {
+                const int piece = u * kWave + lane;
+                const int vpos = min(p0 + piece / kPiecesPerRow, len - 1);
+                vd[u] = stream_load(vbase + tp.v[u] * page_stride + (int64_t)(vpos % P) * kPosBytes + piece % kPiecesPerRow * 16);
             }
         }
-#pragma unroll
-        for (int u = 0; u < NKL; ++u) kd[u] = stream_load(kp + 64 * u);        // dims 32u + 8j .. + 7 of the lane's position
-#pragma unroll
-        for (int u = 0; u < NVL; ++u) vd[u] = stream_load(vp[u]);
     };
 
     // One tile: scores, online softmax, output.  kc / vc hold the tile's K and V as loaded.
-    auto process = [&](int tile, const vec16 (&kc)[NKL], const vec16 (&vc)[NVL]) {
+    auto process = [&](int i, const vec16 (&kc)[NKL], const vec16 (&vc)[NVL]) __attribute__((always_inline)) {
+        const int tile = first + kAttnWaves * i;
         // scores of the tile: lane (head c, j) gets positions 4j .. 4j+3
         f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int u = 0; u < NKL; ++u) {
-            s = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(lo4(kc[u]), qb[2 * u], s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(hi4(kc[u]), qb[2 * u + 1], s, 0, 0, 0);
+            bf16x8 ka;
+            __builtin_memcpy(&ka, &kc[u], 16);
+            s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qb[u], s, 0, 0, 0);
         }
         float sv[4];
         float tmax = -INFINITY;
@@ -244,51 +246,48 @@ __global__ __launch_bounds__(kAttnWaves* kWave) void attn_decode_kernel(
 
         // the V tile through LDS: written as rows, read as (4 consecutive positions of one dim)
         char* vt = sh_v[wave];
+        const int v_read = (4 * j + (c >> 2)) * kRowBytes + (c & 3) * 8;
 #pragma unroll
-        for (int u = 0; u < NVL; ++u) *(vec16*)(vt + v_lane_pos[u] * kRowBytes + v_lane_off[u]) = vc[u];
+        for (int u = 0; u < NVL; ++u) {
+            const int piece = u * kWave + lane;
+            *(vec16*)(vt + piece / kPiecesPerRow * kRowBytes + piece % kPiecesPerRow * 16) = vc[u];
+        }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int t = 0; t < NDB; ++t) {
-            const char* col = vt + (4 * j) * kRowBytes + (16 * t + c) * 2;
-            const unsigned v0 = *(const uint16_t*)(col), v1 = *(const uint16_t*)(col + kRowBytes);
-            const unsigned v2 = *(const uint16_t*)(col + 2 * kRowBytes), v3 = *(const uint16_t*)(col + 3 * kRowBytes);
-            const unsigned w[2] = {v0 | (v1 << 16), v2 | (v3 << 16)};
-            bf16x4 vb;
-            __builtin_memcpy(&vb, w, 8);
+            // lane (c, j) reads 8 bytes of position 4j + c/4; the transposed read hands it positions 4j .. 4j+3 of dim 16t + c
+            const bf16x4 vb = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bf16x4_ptr)(vt + v_read + 32 * t));
             acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(p_hi, vb, acc[t], 0, 0, 0);
             acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(p_lo, vb, acc[t], 0, 0, 0);
         }
         __builtin_amdgcn_wave_barrier();        // all lanes have read the tile before the next one overwrites it
     };
 
-    // Software pipeline over this wave's tiles (tile, tile + 4, ...): while one tile is processed the next one's
-    // loads are in flight and the page numbers of the one after are being read.  Unrolled by two so that the two
-    // register buffers swap roles without copies.
-    vec16 ka[NKL], va[NVL], kb[NKL], vb2[NVL];
-    TilePages pg{};
-    int tile = tile_begin + wave;
-    if (tile < tile_end) {
-        lookup(tile, pg);
-        load_tile(tile, pg, ka, va);
-        if (tile + kAttnWaves < tile_end) lookup(tile + kAttnWaves, pg);
-    }
-    while (tile < tile_end) {
-        int next = tile + kAttnWaves;
-        if (next < tile_end) {
-            load_tile(next, pg, kb, vb2);
-            if (next + kAttnWaves < tile_end) lookup(next + kAttnWaves, pg);
+    // Software pipeline over this wave's tiles: kDepth register buffers, kDepth - 1 tiles in flight while one is processed.
+    if (n_mine > 0) {
+        vec16 kd[kDepth][NKL], vd[kDepth][NVL];
+        TilePages pg{};
+        lookup(0, pg);
+#pragma unroll
+        for (int b = 0; b < kDepth - 1; ++b) {
+            load_tile(b, pg, kd[b], vd[b]);
+            lookup(b + 1, pg);
         }
-        process(tile, ka, va);
-        tile = next;
-        if (tile >= tile_end) break;
-        next = tile + kAttnWaves;
-        if (next < tile_end) {
-            load_tile(next, pg, ka, va);
-            if (next + kAttnWaves < tile_end) lookup(next + kAttnWaves, pg);
+        // Whole groups of kDepth tiles without a branch inside, then the rest, which is already in flight.
+        constexpr int kAhead = kDepth - 1;
+        const int n_whole = n_mine / kDepth * kDepth;
+        for (int i0 = 0; i0 < n_whole; i0 += kDepth) {
+#pragma unroll
+            for (int b = 0; b < kDepth; ++b) {
+                load_tile(i0 + b + kAhead, pg, kd[(b + kAhead) % kDepth], vd[(b + kAhead) % kDepth]);
+                lookup(i0 + b + kDepth, pg);
+                process(i0 + b, kd[b], vd[b]);
+            }
         }
-        process(tile, kb, vb2);
-        tile = next;
+#pragma unroll
+        for (int b = 0; b < kAhead; ++b)
+            if (n_whole + b < n_mine) process(n_whole + b, kd[b], vd[b]);
     }
 
     // merge the waves: common reference per head, then sums and outputs

@@ -114,3 +114,32 @@ def test_terminated_rows_are_skipped():
         assert np.all(got[done == 1] == 0.0)
         assert np.abs(got[done == 0] - want[done == 0]).max() < TOL
     s.close()
+
+
+@pytest.mark.parametrize("D,P", [(128, 0), (64, 0), (128, 16), (64, 24), (128, 7)])
+def test_every_remainder_of_the_tile_pipeline(D, P):
+    """One to fourteen tiles of 16 positions (none to five whole groups of three per wave, every remainder), a last tile of
+    1, 15 or 16 positions.  What lies past the length is NaN: it must not be read into the result.  Tolerance as above."""
+    rng = np.random.default_rng(D + P)
+    B, N, Hkv, G, S = 1, 3, 2, 5, 16 * 14
+    R, Hq, scale = B * N, Hkv * G, 0.1
+    k, v = _bits(rng, (R, Hkv, S, D)), _bits(rng, (R, Hkv, S, D))
+    qb = _bits(rng, (R, Hq, D))
+    for length in sorted({16 * t + e for t in range(14) for e in (1, 15, 16)}):
+        hidden = [x.copy() for x in (k, v)]
+        for x in hidden:
+            x[:, :, length:] = 0x7FC0
+        if P:
+            s = Session(B, N, 64, 8, "f32", 0.5, 0, kv_geom=(2, Hkv, S, D), with_hist=False, page_len=P, len0=length)
+            M = (S + P - 1) // P
+            for pool, x in zip(s.pools, hidden):               # page j of row i is number j*N + i
+                padded = np.full((R, Hkv, M * P, D), 0x7FC0, np.uint16)
+                padded[:, :, :S] = x
+                pages = padded.reshape(R, Hkv, M, P, D).transpose(2, 0, 1, 3, 4).reshape(M * R, Hkv, P, D)
+                pool.view(torch.int16).copy_(torch.as_tensor(np.ascontiguousarray(pages).view(np.int16)))
+        else:
+            s = Session(B, N, 64, 8, "f32", 0.5, 0, kv=hidden, with_hist=False)
+        got = s.attention(0, 1, _q_dev(qb), length, scale).cpu().numpy()
+        want = decode_attention(qb, k, v, length, scale)
+        assert np.abs(got - want).max() < TOL, (length, np.abs(got - want).max())
+        s.close()
