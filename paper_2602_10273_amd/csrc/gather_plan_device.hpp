@@ -1,10 +1,8 @@
-// Device side of the reorder's plan (Alg. 1 "reorder KV cache by A"; App. C): one wave groups the moved rows of one
-// resampled prompt by ancestor for the gather kernel.  In a header because two kernels run it: the plan kernel of
-// smc_kv_reindex, and the resampling kernel when the reorder follows in the same call (the wave that resampled a
-// prompt goes on to plan it).
+// Device side of the reorder's plan (Alg. 1 "reorder KV cache by A"; App. C): a team of threads groups the moved rows of
+// one resampled prompt by ancestor for the gather kernel.  In a header because several kernels run it: the plan kernel of
+// smc_kv_reindex, and, when the reorder follows in the same call, whatever resampled the prompt goes on to plan it.
 #pragma once
-#include "device_rng.hpp"
-#include "smc_internal.hpp"
+#include "weights_device.hpp"
 
 namespace psmc {
 
@@ -16,78 +14,76 @@ struct PlanArgs {
     double* cumlogp; int32_t* done; int32_t* parity;
 };
 
-// The plan of one resampled prompt (one wave).  phase: which of the plan's two group counters this call uses.
-__device__ inline void plan_prompt(const int32_t* __restrict__ anc, int N, int mask_words, int phase, GatherPlan* __restrict__ plan,
-                            int32_t* __restrict__ grp_src, int32_t* __restrict__ grp_base, int32_t* __restrict__ grp_srcpar,
-                            unsigned long long* __restrict__ grp_mask, double* __restrict__ cumlogp,
-                            int32_t* __restrict__ done, int32_t* __restrict__ parity, int skip_terminated)
+// The plan of resampled prompt b by one team.  phase: which of the plan's two group counters this call uses.
+// The caller has filled and synchronised sh.anc (ancestors within the prompt; -1: the row is left untouched), sh.cum,
+// sh.done and sh.par (the rows' state before the reorder).
+__device__ inline void plan_prompt(const PlanArgs& pl, int b, int phase, const Team& tm, const PromptLds& sh)
 {
-    __shared__ int32_t sh_anc[SMC_MAX_PARTICLES];
-    __shared__ double sh_cum[SMC_MAX_PARTICLES];
-    __shared__ int32_t sh_done[SMC_MAX_PARTICLES];
-    __shared__ int32_t sh_first[SMC_MAX_PARTICLES];                // lowest moved row that continues each ancestor
-    __shared__ int32_t sh_group[SMC_MAX_PARTICLES];                // group number of each ancestor that has one
-    __shared__ int32_t sh_base;
-    const int b = blockIdx.x, lane = threadIdx.x;
-    const int row0 = b * N;
-    int bad = 0;
-    for (int k = lane; k < N; k += kWave) {
-        int a = anc[row0 + k] - row0;
-        if (a < 0 || a >= N) { a = -1; ++bad; }                    // outside the prompt: row is left untouched
-        if (a == k) a = -1;                                        // its own ancestor: nothing to move
-        sh_anc[k] = a;
-        sh_cum[k] = cumlogp[row0 + k];
-        sh_done[k] = done[row0 + k];
+    const int N = pl.N, row0 = b * N;
+    int32_t* const first = reinterpret_cast<int32_t*>(sh.b);       // lowest moved row that continues each ancestor
+    int32_t* const group = first + pad_serial(N);                  // group number of each ancestor that has one
+    int* const sh_base = reinterpret_cast<int*>(sh.red);
+    // descendants of each ancestor as a bit set over the prompt's rows: in LDS where one word holds them (N <= 64)
+    unsigned long long* const desc = reinterpret_cast<unsigned long long*>(sh.a);
+    const bool one_word = pl.mask_words == 1;
+    for (int k = tm.tid; k < N; k += tm.n) { first[k] = N; desc[k] = 0ull; }
+    tm.sync();
+    for (int k = tm.tid; k < N; k += tm.n) {
+        const int a = sh.anc[k];
+        if (a < 0 || a == k) continue;                             // a row that is its own ancestor has nothing to move
+        atomicMin(&first[a], k);
+        if (one_word) atomicOr(&desc[a], 1ull << k);
     }
-    __syncthreads();
+    tm.sync();
     // leaders: first moved row (in particle order) of each distinct ancestor
-    for (int k = lane; k < N; k += kWave) sh_first[k] = N;
-    __syncthreads();
-    for (int k = lane; k < N; k += kWave)
-        if (sh_anc[k] >= 0) atomicMin(&sh_first[sh_anc[k]], k);
-    __syncthreads();
-    int n_lead = 0;
-    for (int k0 = 0; k0 < N; k0 += kWave) {
-        const int k = k0 + lane;
-        const bool lead = k < N && sh_anc[k] >= 0 && sh_first[sh_anc[k]] == k;
-        n_lead += __popcll(__ballot(lead));
-    }
-    if (lane == 0) sh_base = n_lead ? atomicAdd(&plan->n_groups[phase], n_lead) : 0;
-    for (int o = 32; o > 0; o >>= 1) bad += __shfl_xor(bad, o);
-    if (lane == 0 && bad) atomicAdd(&plan->bad_anc, bad);
-    __syncthreads();
-    int placed = 0;
-    for (int k0 = 0; k0 < N; k0 += kWave) {
-        const int k = k0 + lane;
-        const bool lead = k < N && sh_anc[k] >= 0 && sh_first[sh_anc[k]] == k;
-        const unsigned long long mk = __ballot(lead);
-        if (lead) {
-            const int a = sh_anc[k];
-            const int g = sh_base + placed + mask_rank(mk);
-            grp_src[g] = row0 + a;
-            grp_base[g] = row0;
-            // bit 0: the ancestor's live buffer, before any flip; bit 1 (only where the caller opted in and an
-            // end-of-sequence token is configured): the ancestor has terminated -- its cache is never read again
-            // (App. D: the absorbing state is a no-op), so its KV rows are not copied
-            grp_srcpar[g] = parity[row0 + a] | ((skip_terminated && sh_done[a]) ? 2 : 0);
-            for (int w = 0; w < mask_words; ++w) grp_mask[(int64_t)g * mask_words + w] = 0ull;
-            sh_group[a] = g;
+    if (tm.first_wave()) {
+        int n_lead = 0;
+        for (int k0 = 0; k0 < N; k0 += kWave) {
+            const int k = k0 + tm.tid;
+            const bool lead = k < N && sh.anc[k] >= 0 && sh.anc[k] != k && first[sh.anc[k]] == k;
+            const unsigned long long mk = __ballot(lead);
+            if (lead) group[sh.anc[k]] = n_lead + mask_rank(mk);
+            n_lead += __popcll(mk);
         }
-        placed += __popcll(mk);
+        if (tm.tid == 0) *sh_base = n_lead ? atomicAdd(&pl.plan->n_groups[phase], n_lead) : 0;
     }
-    __syncthreads();                                               // group numbers known, bit sets cleared
-    for (int k = lane; k < N; k += kWave) {
-        const int a = sh_anc[k];
-        if (a >= 0) atomicOr(&grp_mask[(int64_t)sh_group[a] * mask_words + (k >> 6)], 1ull << (k & 63));
+    tm.sync();
+    const int base = *sh_base;
+    for (int k = tm.tid; k < N; k += tm.n) {
+        const int a = sh.anc[k];
+        if (a < 0 || a == k || first[a] != k) continue;
+        const int g = base + group[a];
+        pl.grp_src[g] = row0 + a;
+        pl.grp_base[g] = row0;
+        // bit 0: the ancestor's live buffer, before any flip; bit 1 (only where the caller opted in and an
+        // end-of-sequence token is configured): the ancestor has terminated -- its cache is never read again
+        // (App. D: the absorbing state is a no-op), so its KV rows are not copied
+        pl.grp_srcpar[g] = sh.par[a] | ((pl.skip_terminated && sh.done[a]) ? 2 : 0);
+        if (one_word) pl.grp_mask[g] = desc[a];
+        else for (int w = 0; w < pl.mask_words; ++w) pl.grp_mask[(int64_t)g * pl.mask_words + w] = 0ull;
     }
-    __syncthreads();                                               // every group has recorded its source parity
-    for (int k = lane; k < N; k += kWave) {
-        const int a = sh_anc[k];
-        if (a >= 0) {
-            cumlogp[row0 + k] = sh_cum[a];
-            done[row0 + k] = sh_done[a];
-            parity[row0 + k] ^= 1;                                 // from now on: the buffer this row is written to
-        }
+    if (!one_word) {                                               // the leaders have cleared, now every moved row adds itself
+        __builtin_amdgcn_s_waitcnt(0x0F70);                        // vmcnt(0): the zeros precede the atomics
+        tm.sync();
+    }
+    for (int k = tm.tid; k < N; k += tm.n) {
+        const int a = sh.anc[k];
+        if (a < 0 || a == k) continue;
+        if (!one_word) atomicOr(&pl.grp_mask[(int64_t)(base + group[a]) * pl.mask_words + (k >> 6)], 1ull << (k & 63));
+        pl.cumlogp[row0 + k] = sh.cum[a];
+        pl.done[row0 + k] = sh.done[a];
+        pl.parity[row0 + k] = sh.par[k] ^ 1;                       // from now on: the buffer this row is written to
+    }
+}
+
+// What plan_prompt wants to find in LDS, from global memory.
+__device__ inline void load_plan_state(const PlanArgs& pl, int b, const Team& tm, const PromptLds& sh)
+{
+    for (int k = tm.tid; k < pl.N; k += tm.n) {
+        const int row = b * pl.N + k;
+        sh.cum[k] = pl.cumlogp[row];
+        sh.done[k] = pl.done[row];
+        sh.par[k] = pl.parity[row];
     }
 }
 

@@ -9,7 +9,7 @@
 // Moved rows that share an ancestor form a group: the ancestor's bytes are read ONCE into registers and stored to
 // every member, so a reindex moves (distinct ancestors of moved rows + moved rows) rows, the least the method allows.
 //
-//   plan_kernel    : one wave per prompt.  Builds the groups (ancestor row, which of its buffers is live and whether
+//   plan_kernel    : one team of threads per prompt.  Builds the groups (ancestor row, which of its buffers is live and whether
 //                    it has terminated, bit set of moved descendants), gathers cumulative log p and termination flags the same way, and flips
 //                    the parity of the moved rows -- so after it, a moved row's parity names the buffer to WRITE.
 //   gather_kernel  : persistent grid-stride loop over (group, tensor, head chunk, slab of 8..64 KiB) for the KV
@@ -22,14 +22,27 @@ namespace {
 typedef unsigned int vec16 __attribute__((ext_vector_type(4)));    // one 16-byte global load / store
 }  // namespace
 
-// One wave per prompt.
-__global__ __launch_bounds__(kWave) void plan_kernel(const int32_t* __restrict__ anc, const int32_t* __restrict__ resampled,
-                                                     PlanArgs pl)
+// One workgroup per prompt.
+__global__ __launch_bounds__(kTeamThreads) void plan_kernel(const int32_t* __restrict__ anc, const int32_t* __restrict__ resampled,
+                                                            PlanArgs pl)
 {
+    extern __shared__ __align__(16) unsigned char team_lds[];
+    const int b = blockIdx.x;
     const int phase = pl.plan->phase;
-    if (resampled[blockIdx.x])
-        plan_prompt(anc, pl.N, pl.mask_words, phase, pl.plan, pl.grp_src, pl.grp_base, pl.grp_srcpar, pl.grp_mask, pl.cumlogp,
-                    pl.done, pl.parity, pl.skip_terminated);
+    if (resampled[b]) {
+        const Team tm{(int)threadIdx.x, (int)blockDim.x};
+        const PromptLds sh(team_lds, pl.N);
+        int bad = 0;
+        for (int k = tm.tid; k < pl.N; k += tm.n) {
+            int a = anc[(int64_t)b * pl.N + k] - b * pl.N;
+            if (a < 0 || a >= pl.N) { a = -1; ++bad; }             // outside the prompt: row is left untouched
+            sh.anc[k] = a;
+        }
+        load_plan_state(pl, b, tm, sh);
+        if (bad) atomicAdd(&pl.plan->bad_anc, bad);
+        tm.sync();
+        plan_prompt(pl, b, phase, tm, sh);
+    }
     plan_finish(pl.plan, phase, (int)gridDim.x);
 }
 
@@ -166,7 +179,8 @@ hipError_t launch_reindex(smc_ctx* c, const int32_t* anc, const int32_t* resampl
     const bool have_kv = c->kv_bound && cfg.kv_tensors > 0 && valid_len > 0;
     const bool have_hist = c->hist_bound && (t > 0 || c->device_step);
     if (!planned)
-        hipLaunchKernelGGL(plan_kernel, dim3(cfg.B), dim3(kWave), 0, c->stream, anc, resampled, plan_args(c));
+        hipLaunchKernelGGL(plan_kernel, dim3(cfg.B), dim3(team_threads(cfg.N)), PromptLds::plan_bytes(cfg.N), c->stream, anc, resampled,
+                           plan_args(c));
     if (have_kv || have_hist) {
         GatherGeom kv{}, hist{};
         if (have_kv) {

@@ -399,20 +399,22 @@ __device__ inline void finalize_done_row(const StepArgs& a, const StepScalars& s
 }
 
 // After a row is final: with resampling folded into this launch, the wave that completes a prompt resamples it.
-// lds: at least 2*N doubles + one int, free for this wave's use.
+// lds: PromptLds::weight_bytes(N), free for this wave's use.
 __device__ inline void after_row_final(const StepArgs& a, const StepScalars& sc, uint32_t row, unsigned char* lds)
 {
     if (!a.fuse_resample) return;
-    const int lane = lane_id();
-    const int b = (int)row / a.rs.N;
+    const int N = a.rs.N;
+    const int b = (int)row / N;
     const int tk = take_ticket(&a.prompt_ticket[b]);   // this row's weight has been written
-    if (tk != a.rs.N - 1) return;
-    if (lane == 0) store_shared(&a.prompt_ticket[b], 0);   // nobody else touches it until the next step
+    if (tk != N - 1) return;
+    const Team tm{lane_id(), kWave};
+    if (tm.tid == 0) store_shared(&a.prompt_ticket[b], 0);   // nobody else touches it until the next step
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup"); // (keeps the reads below behind the ticket)
-    double* sh_a = reinterpret_cast<double*>(lds);
-    double* sh_b = sh_a + a.rs.N;
-    int* sh_k = reinterpret_cast<int*>(sh_b + a.rs.N);
-    resample_prompt(a.rs, a.logW, b, sc.step, sh_a, sh_b, sh_k);
+    const PromptLds sh(lds, N);
+    // at agent scope: other workgroups may have written these weights a moment ago
+    for (int i = tm.tid; i < N; i += tm.n) sh.w[i] = load_shared(a.logW + (int64_t)b * N + i);
+    tm.sync();
+    resample_prompt(a.rs, a.logW + (int64_t)b * N, b, sc.step, tm, sh);
 }
 
 }  // namespace
@@ -435,7 +437,7 @@ __global__ __launch_bounds__(NW * kWave, 4) void vocab_pass_kernel(const StepArg
     constexpr int kScoreAsVectors = 160;
     // LDS: the candidate rings while streaming; afterwards the same bytes serve the resampling of a prompt
     constexpr int kRingBytes = DENSE ? 0 : NW * (kRingV * 20 + kRingE * 8);
-    constexpr int kTailBytes = 2 * SMC_MAX_PARTICLES * 8 + 16;
+    constexpr int kTailBytes = (int)PromptLds::weight_bytes(SMC_MAX_PARTICLES);
     constexpr int kLdsBytes = kRingBytes > kTailBytes ? kRingBytes : kTailBytes;
     __shared__ __align__(16) unsigned char lds[kLdsBytes];
     __shared__ int wg_bound;                           // best "cannot win below this" bound of the whole workgroup
