@@ -63,16 +63,44 @@ template <int DT>
 __device__ __forceinline__ float vec_max(const float (&x)[Elems<DT>::kPerVec])
 {
     if constexpr (DT == SMC_BF16)
-        return fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
+        return fmaxf(fmaxf(fmaxf(x[3], x[4]), x[5]), fmaxf(fmaxf(x[6], x[7]), fmaxf(fmaxf(x[0], x[1]), x[2])));   // four v_max3
     else
         return fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
 }
 
-template <int DT>
-__device__ __forceinline__ float load_scalar(const void* row, int64_t i)
+// bf16 rows form the exponent straight from the logit, fp32 rows from its distance to the maximum
+template <int DT> constexpr bool kDirectOf = DT == SMC_BF16;
+
+// A buffer descriptor over `bytes` bytes (a multiple of 16) from p, both equal on every lane; loads past its end return 0.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t slice_descriptor(const void* p, int bytes)
 {
-    if constexpr (DT == SMC_BF16) return __uint_as_float((uint32_t)((const uint16_t*)row)[i] << 16);
-    else return ((const float*)row)[i];
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00027000);
+}
+// every logit is read exactly once: non-temporal loads keep the stream out of the caches
+__device__ __forceinline__ uint4 load_stream(__amdgpu_buffer_rsrc_t rsrc, int offset)
+{
+    const vec16 r = __builtin_amdgcn_raw_buffer_load_b128(rsrc, offset, 0, 2);
+    return make_uint4(r.x, r.y, r.z, r.w);
+}
+
+// The ragged last vector of a row (V not a multiple of the vector width), -inf where the row has ended.
+template <int DT>
+__device__ __forceinline__ uint4 load_tail(const char* rowp, int V)
+{
+    constexpr int EPV = Elems<DT>::kPerVec;
+    const int first = V / EPV * EPV;
+    uint32_t w[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if constexpr (DT == SMC_BF16) {
+            const int i = first + 2 * k;
+            const uint32_t lo = i < V ? ((const uint16_t*)rowp)[i] : 0xFF80u, hi = i + 1 < V ? ((const uint16_t*)rowp)[i + 1] : 0xFF80u;
+            w[k] = lo | (hi << 16);
+        } else {
+            w[k] = first + k < V ? ((const uint32_t*)rowp)[first + k] : 0xFF800000u;
+        }
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
 // e^P for small integer P by multiplication
@@ -165,8 +193,8 @@ __device__ __forceinline__ int take_ticket(int32_t* ticket)
 
 template <int NW>
 __device__ __forceinline__ void block_epilogue(float beta, float m_wave, float M1, float Mb, float s1, float sb,
-                                               const LaneTop2 top, unsigned long long n_scored,
-                                               unsigned long long n_drains, Partial* __restrict__ out, Partial* lds_copy)
+                                               const LaneTop2 top, int n_scored, int n_drains,
+                                               Partial* __restrict__ out, Partial* lds_copy)
 {
     static_assert(2 * NW <= kWave, "one wave merges two candidates per wave");
     __shared__ float red_f[NW][5];
@@ -188,7 +216,7 @@ __device__ __forceinline__ void block_epilogue(float beta, float m_wave, float M
             red_cl[wave][1] = sec_b ? top.b.l : top.a.l; red_cg[wave][1] = sec_b ? top.b.g : top.a.g;
             red_ci[wave][1] = sec_b ? top.b.i : top.a.i;
         }
-        const int sc = wave_sum_i32((int)n_scored);
+        const int sc = wave_sum_i32(n_scored);
         if (lane == 0) {
             if (lb < 0) red_ci[wave][0] = -1;
             if (l2 < 0) red_ci[wave][1] = -1;
@@ -422,6 +450,13 @@ __device__ inline void after_row_final(const StepArgs& a, const StepScalars& sc,
 // P > 0: beta is the integer P (sum of e^P by multiplication); P == 0: generic beta (second exp2).
 // DENSE: every entry is scored in place (no filter, no ring) -- the plain definition, kept for cross-checks.
 // NW: waves per workgroup (4, 8 or 16).
+// The code is laid out for its size as much as for its speed: what happens rarely (a new maximum, a full ring, scoring)
+// stands at one place each, outside the unrolled stream.  With a copy of it in every unrolled vector the kernel had 29 000
+// instructions (134 KB, twice the instruction cache; now 47 KB), and a launch over few rows spent its time fetching them.
+// Measured (bf16, V = 152064, beta = 4 unless noted): 64 rows 26.8 -> 22.5 us, 128 rows 29.4 -> 26.7, 256 rows at beta = 6
+// 34.0 -> 28.3, 2048 rows 147 -> 141 (VALU-bound: 8066 vector instructions a wave, of which the 74 vectors of its stream
+// take 62 each, scoring 1400 and start and end 760); 2048 fp32 rows unchanged at 6.2 TB/s.  Summing on the matrix cores
+// (v_mfma_f32_4x4x1, one entry per lane) instead of the vector ALUs was slower (182 us for 2048 rows).
 template <int DT, int P, bool DENSE, int NW>
 __global__ __launch_bounds__(NW * kWave, 4) void vocab_pass_kernel(const StepArgs a)
 {
@@ -430,11 +465,12 @@ __global__ __launch_bounds__(NW * kWave, 4) void vocab_pass_kernel(const StepArg
     constexpr int UNROLL = 4;                          // 16-byte loads per thread and register set (two sets alternate)
     constexpr int THREADS = NW * kWave;
     constexpr int kRingV = 256;                        // queued vectors per wave (power of two, >= 2 wave-widths)
-    constexpr int kRingE = 128;                        // queued single entries per wave (power of two, 2 wave-widths)
     // A drain that finds more than this many entries still above the bound scores its vectors as they are (one Philox
     // block serves the four entries of a quad); fewer are compacted into the entry ring first, so that every lane of
     // a scoring pass has an entry to score.  The two costs meet at about 2.5 entries per lane.
     constexpr int kScoreAsVectors = 160;
+    constexpr int kRingE = 256;                        // queued single entries per wave: what one drain adds to less than a wave-width
+    static_assert(kScoreAsVectors + kWave <= kRingE, "a drain's entries must fit");
     // LDS: the candidate rings while streaming; afterwards the same bytes serve the resampling of a prompt
     constexpr int kRingBytes = DENSE ? 0 : NW * (kRingV * 20 + kRingE * 8);
     constexpr int kTailBytes = (int)PromptLds::weight_bytes(SMC_MAX_PARTICLES);
@@ -443,39 +479,68 @@ __global__ __launch_bounds__(NW * kWave, 4) void vocab_pass_kernel(const StepArg
     __shared__ int wg_bound;                           // best "cannot win below this" bound of the whole workgroup
     __shared__ Partial sh_part;                        // this workgroup's partial record, for a row of one slice
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // scalar, and with it what the wave keeps count of
     const int n_split = a.n_split;
     const int split = blockIdx.x % n_split;
     const uint32_t row = blockIdx.x / n_split;
     const StepScalars sc = step_scalars(a);
-    if (a.eos_id >= 0 && a.done[row]) {                // terminated particle (App. D): its logits are not read
-        if (split == 0 && wave == 0) {
-            if (lane == 0) finalize_done_row(a, sc, row);
-            after_row_final(a, sc, row, lds);
-        }
-        return;
-    }
+    RowState row_state{};
+    const bool terminated = a.eos_id >= 0 && a.done[row];    // (App. D): the row's logits are not read
+    if (!terminated) {
     uint4* const ring_raw = reinterpret_cast<uint4*>(lds) + (DENSE ? 0 : wave * kRingV);
     uint32_t* const ring_idx = reinterpret_cast<uint32_t*>(lds + (DENSE ? 0 : NW * kRingV * 16)) + (DENSE ? 0 : wave * kRingV);
     uint2* const ring_ent = reinterpret_cast<uint2*>(lds + (DENSE ? 0 : NW * kRingV * 20)) + (DENSE ? 0 : wave * kRingE);
     const char* rowp = (const char*)a.logits + (int64_t)row * a.row_stride_bytes;
     const int V = a.V;
     const uint32_t key0 = a.key0, key1 = a.key1, step = sc.step;
-    if (tid == 0) wg_bound = enc_bound(-INFINITY);
-    __syncthreads();
-    RowState row_state{};
-    if (wave == 0) row_state = load_row_state(a, row);    // wave-uniform (scalar) reads, consumed by the tail
 
     const int nvec_full = V / EPV;                      // vectors wholly inside the row
     const int nvec = (V + EPV - 1) / EPV;
     const int vec_begin = split * a.vecs_per_split;
     const int vec_end = min(vec_begin + a.vecs_per_split, nvec);
 
+    constexpr uint32_t kPadWord = DT == SMC_BF16 ? 0xFF80FF80u : 0xFF800000u;      // -inf in every element
+
+    // The main stream covers the vectors that lie wholly inside the row; the ragged last vector of a row (V not a
+    // multiple of the vector width) is handled before it.  Loads go through a buffer descriptor that ends with the slice:
+    // one past the end costs no memory access and returns zeros, so every batch is loaded by the same four instructions
+    // without a branch or a clamp, and the next batch's loads are under way while one is processed.  (Clamped loads behind
+    // a branch made the compiler wait for each of the four in turn in a slice's last batch, and for everything in flight
+    // before the next batch's loads.)
+    const int full_end = min(vec_end, nvec_full);
+    constexpr int kBatch = THREADS * UNROLL;
+    // Two register sets of UNROLL vectors per thread alternate: while one batch is processed the next is in flight.
+    auto load_batch = [&](uint4 (&dst)[UNROLL], int b0) __attribute__((always_inline)) {
+        const int left = full_end - b0;                 // vectors of the slice from b0 on
+        const auto rsrc = slice_descriptor(rowp + (int64_t)b0 * 16, left < kBatch ? (left > 0 ? left * 16 : 0) : kBatch * 16);
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) dst[u] = load_stream(rsrc, (u * THREADS + tid) * 16);
+    };
+    // -inf in place of the zeros past the slice: such an entry adds 0 to the sums and never passes the filter
+    auto pad_batch = [&](uint4 (&src)[UNROLL], int b0) __attribute__((always_inline)) {
+        if (b0 + kBatch > full_end) {
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) {
+                const bool pad = b0 + u * THREADS + tid >= full_end;
+                src[u].x = pad ? kPadWord : src[u].x; src[u].y = pad ? kPadWord : src[u].y;
+                src[u].z = pad ? kPadWord : src[u].z; src[u].w = pad ? kPadWord : src[u].w;
+            }
+        }
+    };
+    uint4 buf_a[UNROLL], buf_b[UNROLL];
+    load_batch(buf_a, vec_begin);
+    const bool has_tail = nvec > nvec_full && vec_end == nvec && wave == 0;
+    uint4 tail_raw = make_uint4(kPadWord, kPadWord, kPadWord, kPadWord);   // the ragged last vector: lane 0 of wave 0
+    if (has_tail && lane == 0) tail_raw = load_tail<DT>(rowp, V);
+
+    if (tid == 0) wg_bound = enc_bound(-INFINITY);
+    __syncthreads();
+    if (wave == 0) row_state = load_row_state(a, row);    // wave-uniform (scalar) reads, consumed by the tail
+
     const float beta = (float)sc.beta;
     const float beta_l2e = beta * kLog2e;
     const float window = (kGumbelMax - kGumbelMin + kKeyMargin) / beta;   // in logit units
-
-    constexpr uint32_t kPadWord = DT == SMC_BF16 ? 0xFF80FF80u : 0xFF800000u;      // -inf in every element
 
     // wave-uniform running state
     float m = -3.0e38f;            // running max of the logits seen by this wave
@@ -488,10 +553,14 @@ __global__ __launch_bounds__(NW * kWave, 4) void vocab_pass_kernel(const StepArg
     float s1 = 0.f, sb = 0.f;      // per-lane sums relative to the references
     float thr_rel = -3.4e38f;      // the filter bound in the units the stream works in, rounded down: thr - m where the
                                    // stream forms d = x - m (fp32 rows), thr*log2e - M1 where it forms t = x*log2e - M1 (bf16 rows)
-    float t_max = -3.4e38f;        // bf16 rows: m in those units, t_max = m*log2e - M1
+    float t_max = kDirectOf<DT> ? -3.4e38f : 0.f;      // m in those units: m*log2e - M1, or 0
+    float jump_rel = -3.4e38f;     // an entry above this (in those units) lies too far above the running maximum to be added
+    float keep_rel = -3.4e38f;     // a vector whose entries all lie below this (in those units) neither holds a possible
+                                   // winner nor adds to the sum of exp(beta l): see kDropBits
     int q_head = 0, q_count = 0;   // ring of queued vectors
     int e_head = 0, e_count = 0;   // ring of queued single entries (always < 64 between drains)
-    unsigned long long n_scored = 0, n_drains = 0;
+    int overflow = 0, redo = 0;    // bit k: vector k of the running pair of batches did not fit the ring / was left out
+    int n_scored = 0, n_drains = 0;
     LaneTop2 top; top.init();
     // the lane's highest entry among the vectors that raised the wave's running maximum since the last probe
     float probe_l = -INFINITY;
@@ -506,13 +575,23 @@ __global__ __launch_bounds__(NW * kWave, 4) void vocab_pass_kernel(const StepArg
     // 2^(x*kLog2eLow); its bulk 2^(m*kLog2eLow) is a per-wave factor applied to the sums at the end, what remains is
     // below 1e-6 for entries within a hundred units of the maximum (others add nothing).  fp32 rows, whose magnitudes
     // are unbounded and whose stream is bound by HBM anyway, keep the x - m form.
-    constexpr bool kDirect = DT == SMC_BF16;
+    constexpr bool kDirect = kDirectOf<DT>;
     constexpr double kLog2eLow = 1.4426950408889634074 - (double)kLog2e;
+
+    // exp(beta x) is left out of its sum where it is below 2^-drop_bits of the largest term the wave has met: the at most V
+    // terms left out are together below 2^-kDropBits of the sum, a thousandth of the rounding of one fp32 addition.  At
+    // beta = 4 that is what lies 9 below the maximum: nearly every vector of heavy-tailed logits, few of Gaussian ones.
+    constexpr int kDropBits = 34;
+    const float drop_bits = (float)(kDropBits + 32 - __builtin_clz((unsigned)V));
+    const float drop_rel = kDirect ? drop_bits / beta : drop_bits / beta_l2e;
+    // terms stay below 2^12 in the one sum and 2^90 in the other
+    const float jump = fminf(12.f, 90.f / beta) * (kDirect ? 1.f : 1.f / kLog2e);
 
     auto set_thr = [&](float t) __attribute__((always_inline)) {
         thr = fmaxf(thr, t);
         if constexpr (kDirect) thr_rel = fmaf(thr, kLog2e, -M1) - (fabsf(thr) * kLog2e + fabsf(M1)) * 3e-7f;
         else thr_rel = (thr - m) - (fabsf(thr) + fabsf(m)) * 3e-7f;
+        keep_rel = fminf(thr_rel, t_max - drop_rel);
     };
 
     auto raise_max = [&](float nm) __attribute__((always_inline)) {                    // nm > m, wave-uniform
@@ -526,7 +605,8 @@ __global__ __launch_bounds__(NW * kWave, 4) void vocab_pass_kernel(const StepArg
         // fp32 rounding of the SMALL quantity (x-m), not of the large products x*log2e
         c1 = (float)((double)nM1 - (double)nm * 1.4426950408889634074);
         cb = (float)((double)nMb - (double)nm * (double)beta * 1.4426950408889634074);
-        t_max = fmaf(m, kLog2e, -M1);
+        if constexpr (kDirect) t_max = fmaf(m, kLog2e, -M1);
+        jump_rel = t_max + jump;
         set_thr(lower(m - window));
     };
 
@@ -609,25 +689,19 @@ __global__ __launch_bounds__(NW * kWave, 4) void vocab_pass_kernel(const StepArg
         tighten();
     };
 
-    // Takes up to 64 queued vectors (one per lane) off the ring.  Entries still at or above thr are either scored where
-    // they are (many: a flat proposal) or compacted into the entry ring, which is scored whenever it holds a full
-    // wave-width.
-    auto drain = [&](int n) __attribute__((always_inline)) {
-        wave_sync();                                    // ring writes of other lanes, same wave
-        float x[EPV];
-        uint32_t vi = 0u;
-        const bool in = lane < n;
-        {
-            uint4 raw = make_uint4(kPadWord, kPadWord, kPadWord, kPadWord);
-            if (in) {
-                const int slot = (q_head + lane) & (kRingV - 1);
-                raw = ring_raw[slot];
-                vi = ring_idx[slot];
-            }
-            unpack<DT>(raw, x);
+    // Appends the vectors of the lanes in `lanes` (this lane's: raw, vi) to the ring; there must be room for a wave-width.
+    auto push = [&](unsigned long long lanes, bool mine, const uint4& raw, uint32_t vi) __attribute__((always_inline)) {
+        if (mine) {
+            const int slot = (q_head + q_count + mask_rank(lanes)) & (kRingV - 1);
+            ring_raw[slot] = raw;
+            ring_idx[slot] = vi;
         }
-        q_head = (q_head + n) & (kRingV - 1);
-        q_count -= n;
+        q_count += __popcll(lanes);
+    };
+
+    // Scores what may still win among the vectors x, one per lane (`in`): where they are, if that is many entries (a flat
+    // proposal), else by way of the entry ring.
+    auto score_vectors = [&](const float (&x)[EPV], uint32_t vi, bool in) __attribute__((always_inline)) {
         ++n_drains;
         int mine = 0;
 #pragma unroll
@@ -641,16 +715,14 @@ __global__ __launch_bounds__(NW * kWave, 4) void vocab_pass_kernel(const StepArg
             for (int j = 0; j < EPV; ++j) {
                 const bool hit = x[j] >= thr;
                 const unsigned long long mk = __ballot(hit);
-                if (mk) {                               // wave-uniform
-                    if (hit) {
-                        const int slot = (e_head + e_count + mask_rank(mk)) & (kRingE - 1);
-                        ring_ent[slot] = make_uint2(vi * EPV + j, __float_as_uint(x[j]));
-                    }
-                    e_count += __popcll(mk);
-                    if (e_count >= kWave) score_entries(kWave);
+                if (hit) {
+                    const int slot = (e_head + e_count + mask_rank(mk)) & (kRingE - 1);
+                    ring_ent[slot] = make_uint2(vi * EPV + j, __float_as_uint(x[j]));
                 }
+                e_count += __popcll(mk);
             }
         }
+        while (e_count >= kWave) score_entries(kWave);
     };
 
     // Drops queued vectors whose entries have all fallen below thr, keeping the order of the rest.
@@ -678,174 +750,170 @@ __global__ __launch_bounds__(NW * kWave, 4) void vocab_pass_kernel(const StepArg
         q_count = kept;
     };
 
-    // Before a batch of the stream: leaves at most half of the vector ring occupied (one copy of the drain code, outside
-    // the unrolled loop over the batch's vectors).
-    auto make_room = [&]() __attribute__((always_inline)) {
-        if (q_count > kRingV / 2) {                     // wave-uniform, rare
-            compact();
-            while (q_count > kRingV / 2) drain(kWave);
-        }
-    };
-
-    // both sums from d[j] = x[j] - m (fp32 rows) or t[j] = x[j]*log2e - M1 (bf16 rows); the exponents are <= 0 up to rounding
-    auto accumulate = [&](const float (&x)[EPV], const float (&d)[EPV]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < EPV; ++j) {
-            const float e = kDirect ? fast_exp2(d[j]) : fast_exp2(fmaf(d[j], kLog2e, -c1));
-            s1 += e;
-            if constexpr (P > 0) sb += ipow<P>(e);
-            else if constexpr (kDirect) sb += fast_exp2(fmaf(x[j], beta_l2e, -Mb));
-            else sb += fast_exp2(fmaf(d[j], beta_l2e, -cb));
-        }
-    };
+    // The stream works on d[j] = x[j] - m (fp32 rows) or t[j] = x[j]*log2e - M1 (bf16 rows); the exponents are <= 0 up to rounding.
     auto relative = [&](const float (&x)[EPV], float (&d)[EPV]) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < EPV; ++j) d[j] = kDirect ? fmaf(x[j], kLog2e, -M1) : x[j] - m;
     };
-
-    // One vector of the stream: running maximum, filter, sums.  The maximum and the filter work on the relative values
-    // (which the sums need anyway); only when some lane holds an entry above the running maximum is the maximum itself formed.
-    auto stream_vector = [&](const uint4& raw, int vi, bool in_slice) __attribute__((always_inline)) {
-        float x[EPV], d[EPV];
+    // Adds exp(x) to s1 and leaves it in e[] (needed again for an integer beta).
+    auto add_s1 = [&](const float (&d)[EPV], float (&e)[EPV]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < EPV; ++j) {
+            e[j] = kDirect ? fast_exp2(d[j]) : fast_exp2(fmaf(d[j], kLog2e, -c1));
+            s1 += e[j];
+        }
+    };
+    auto add_sb = [&](const float (&x)[EPV], const float (&d)[EPV], const float (&e)[EPV]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < EPV; ++j) {
+            if constexpr (P > 0) sb += ipow<P>(e[j]);
+            else if constexpr (kDirect) sb += fast_exp2(fmaf(x[j], beta_l2e, -Mb));
+            else sb += fast_exp2(fmaf(d[j], beta_l2e, -cb));
+        }
+    };
+    // Notes the lane's highest entry of a vector for the probe.
+    auto note_highest = [&](const uint4& raw, int vi) __attribute__((always_inline)) {
+        float x[EPV];
         unpack<DT>(raw, x);
-        relative(x, d);
-        float dm = vec_max<DT>(d);
-        if (__ballot(dm > (kDirect ? t_max : 0.f))) {   // wave-uniform, rare
-            const float lx = vec_max<DT>(x);
-            const float nm = wave_max_f32(lx);
-            if (nm > m) {
-                raise_max(nm);
-                if constexpr (!DENSE) {
-                    probe_pending = true;
-                    if (in_slice && lx > probe_l) {
-                        int jm = EPV - 1;
+        const float lx = vec_max<DT>(x);
+        if (lx > probe_l) {                              // (vectors past the slice are -inf and never the highest)
+            int jm = EPV - 1;
 #pragma unroll
-                        for (int j = EPV - 2; j >= 0; --j) jm = x[j] == lx ? j : jm;
-                        probe_l = lx;
-                        probe_i = (uint32_t)vi * EPV + (uint32_t)jm;
-                    }
-                }
-            }
-            relative(x, d);
-            dm = vec_max<DT>(d);
+            for (int j = EPV - 2; j >= 0; --j) jm = x[j] == lx ? j : jm;
+            probe_l = lx;
+            probe_i = (uint32_t)vi * EPV + (uint32_t)jm;
         }
-        if constexpr (DENSE) {
-            if (in_slice) score_vector(x, (uint32_t)vi, -INFINITY);                  // padding has no index to score
-        } else {
-            // Scoring is deferred: a vector that holds an entry which may still win is only queued here.  By the
-            // time the queue is scored the row's bound is far better than what this wave knows now, and most
-            // entries drop out.
-            const bool hit = dm >= thr_rel;
-            const unsigned long long lanes = __ballot(hit);
-            if (lanes) {                                                              // wave-uniform branch
-                if (q_count <= kRingV - kWave) {
-                    if (hit) {
-                        const int slot = (q_head + q_count + mask_rank(lanes)) & (kRingV - 1);
-                        ring_raw[slot] = raw;
-                        ring_idx[slot] = (uint32_t)vi;
-                    }
-                    q_count += __popcll(lanes);
-                } else {
-                    // the ring is full although it was at most half full when the batch began: so many entries may still
-                    // win (a flat proposal) that scoring the vector where it is costs no more than queueing it would
-                    if (hit) score_vector(x, (uint32_t)vi, thr);
-                    tighten();
-                }
-            }
-        }
-        accumulate(x, d);
     };
 
-    // The main stream covers the vectors that lie wholly inside the row; the ragged last vector of a row (V not a
-    // multiple of the vector width) is handled after it.  A batch that lies wholly inside the slice is loaded without
-    // any guard; only the last, partial batch pays for clamped addresses and selects (-inf where there is no vector:
-    // such an entry adds 0 to the sums and never passes the filter).
-    const int full_end = min(vec_end, nvec_full);
-    constexpr int kBatch = THREADS * UNROLL;
-    // vector u of the batch that starts at b0; `whole`: the batch lies wholly inside the slice (wave-uniform)
-    auto load_vec = [&](int b0, int u, bool whole) __attribute__((always_inline)) -> uint4 {
-        const int vi = b0 + u * THREADS + tid;
-        if (whole) {
-            // every logit is read exactly once: non-temporal loads keep the stream out of the caches
-            const vec16 r = __builtin_nontemporal_load((const vec16*)(rowp + (int64_t)vi * 16));
-            return make_uint4(r.x, r.y, r.z, r.w);
-        }
-        const int vc = min(vi, full_end - 1);
-        uint4 r = *(const uint4*)(rowp + (int64_t)vc * 16);
-        const bool pad = vi >= full_end;
-        r.x = pad ? kPadWord : r.x; r.y = pad ? kPadWord : r.y;
-        r.z = pad ? kPadWord : r.z; r.w = pad ? kPadWord : r.w;
-        return r;
-    };
-
-    // Two register sets of UNROLL vectors per thread alternate: while one batch is processed the next is in flight.
-    auto load_batch = [&](uint4 (&dst)[UNROLL], int b0) __attribute__((always_inline)) {
-        const bool whole = b0 + kBatch <= full_end;
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) dst[u] = load_vec(b0, u, whole);
-    };
-    auto stream_batch = [&](const uint4 (&src)[UNROLL], int b0) __attribute__((always_inline)) {
-        if constexpr (!DENSE) { publish(); adopt(); make_room(); }   // no waiting: whatever the other waves have found so far
+    // One batch of the stream: sums, filter, running maximum.  The maximum and the filter work on the relative values, which
+    // the sums need anyway.  A batch is added against the references as they stood before it: an entry above the running
+    // maximum only makes its terms larger than one.  The maximum is raised behind the batch; a vector so far above it that
+    // its terms could overflow is left out and taken up again then (`redo`).
+    auto stream_batch = [&](uint4 (&src)[UNROLL], int b0, int bit0) __attribute__((always_inline)) {
+        if constexpr (!DENSE) { publish(); adopt(); }    // no waiting: whatever the other waves have found so far
+        float dm[UNROLL];
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
             const int vi = b0 + u * THREADS + tid;
-            stream_vector(src[u], vi, vi < full_end);
-        }
-        if constexpr (!DENSE) { if (probe_pending) probe(); }
-    };
-    uint4 buf_a[UNROLL], buf_b[UNROLL];
-    if (vec_begin < full_end) {
-        load_batch(buf_a, vec_begin);
-        // warm start: the maximum of the wave's first batch gives a useful threshold at once
-        // (vectors past the slice were loaded as -inf and are never the lane's highest)
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            float x[EPV];
-            unpack<DT>(buf_a[u], x);
-            const uint32_t vi = (uint32_t)(vec_begin + u * THREADS + tid);
-#pragma unroll
-            for (int j = 0; j < EPV; ++j) {
-                if (x[j] > probe_l) { probe_l = x[j]; probe_i = vi * EPV + (uint32_t)j; }
+            float x[EPV], d[EPV], e[EPV];
+            unpack<DT>(src[u], x);
+            relative(x, d);
+            dm[u] = vec_max<DT>(d);
+            if (__ballot(dm[u] > jump_rel)) {                                             // wave-uniform branches
+                redo |= 1 << (bit0 + u);
+            } else {
+                add_s1(d, e);
+                if constexpr (DENSE) {
+                    add_sb(x, d, e);
+                    if (vi < full_end) score_vector(x, (uint32_t)vi, -INFINITY);         // padding has no index to score
+                } else if (__ballot(dm[u] >= keep_rel)) {
+                    add_sb(x, d, e);
+                    // Scoring is deferred: a vector that holds an entry which may still win is only queued here.  By the
+                    // time the queue is scored the row's bound is far better than what this wave knows now, and most
+                    // entries drop out.
+                    const bool hit = dm[u] >= thr_rel;
+                    const unsigned long long lanes = __ballot(hit);
+                    if (lanes) {
+                        if (q_count <= kRingV - kWave) push(lanes, hit, src[u], (uint32_t)vi);
+                        else overflow |= 1 << (bit0 + u);    // a flat proposal: taken up again when the ring has been drained
+                    }
+                }
             }
         }
+        if (__ballot(fmaxf(fmaxf(dm[0], dm[1]), fmaxf(dm[2], dm[3])) > t_max)) {         // rare: an entry above the running maximum
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u)
+                if (__ballot(dm[u] > t_max)) note_highest(src[u], b0 + u * THREADS + tid);
+            const float nm = wave_max_f32(probe_l);
+            if (nm > m) { raise_max(nm); probe_pending = true; }
+        }
+    };
+
+    if (vec_begin < full_end) {
+        // warm start: the maximum of the wave's first batch gives a useful threshold at once
+        pad_batch(buf_a, vec_begin);
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) note_highest(buf_a[u], vec_begin + u * THREADS + tid);
         const float bm = wave_max_f32(probe_l);
         if (bm > m) raise_max(bm);
         probe_pending = true;                            // drawn once the next batch's loads are on their way
     }
-    for (int base = vec_begin; base < full_end; base += 2 * kBatch) {
-        const bool second = base + kBatch < full_end;
-        if (second) load_batch(buf_b, base + kBatch);
-        if constexpr (!DENSE) { if (probe_pending) probe(); }      // (the warm start's: behind the loads just issued)
-        stream_batch(buf_a, base);
-        if (!second) break;
-        if (base + 2 * kBatch < full_end) load_batch(buf_a, base + 2 * kBatch);
-        stream_batch(buf_b, base + kBatch);
-    }
-    if (nvec > nvec_full && vec_end == nvec && wave == 0) {                // the ragged tail: lane 0 of wave 0
-        float x[EPV], d[EPV];
-#pragma unroll
-        for (int j = 0; j < EPV; ++j) {
-            const int v = nvec_full * EPV + j;
-            x[j] = (lane == 0 && v < V) ? load_scalar<DT>(rowp, v) : -INFINITY;
-        }
-        const float vm = vec_max<DT>(x);
-        if (__ballot(vm > m)) { const float nm = wave_max_f32(vm); if (nm > m) raise_max(nm); }
-        // the few entries past the last full vector are scored where they are (-inf padding never reaches the bar)
-        if (lane == 0) score_vector(x, (uint32_t)nvec_full, DENSE ? -3.4e38f : thr);
+    if (has_tail) {
+        float x[EPV], d[EPV], e[EPV];
+        unpack<DT>(tail_raw, x);
+        const float nm = wave_max_f32(vec_max<DT>(x));
+        if (nm > m) raise_max(nm);
         relative(x, d);
-        accumulate(x, d);
-    }
-    if constexpr (!DENSE) {
-        // No barrier here: a wave that is done streaming scores its queue against the bound as the workgroup knows it
-        // now, while slower waves still stream -- a few more entries are scored than with the final bound, but the
-        // scoring overlaps with the stream instead of following it.
-        tighten(); publish(); adopt();
-        while (q_count > 0) {
-            if (q_count > kWave) compact();
-            if (q_count > 0) { drain(min(q_count, kWave)); publish(); adopt(); }
+        add_s1(d, e);
+        add_sb(x, d, e);
+        if constexpr (DENSE) {
+            if (lane == 0) score_vector(x, (uint32_t)nvec_full, -3.4e38f);               // (-inf padding never reaches the bar)
+        } else {
+            const bool hit = vec_max<DT>(d) >= thr_rel;
+            push(__ballot(hit), hit, tail_raw, (uint32_t)nvec_full);
         }
-        if (e_count > 0) score_entries(e_count);
-        publish();
+    }
+    for (int base = vec_begin;; base += 2 * kBatch) {
+        const bool first = base < full_end, second = base + kBatch < full_end, last = base + 2 * kBatch >= full_end;
+        load_batch(buf_b, base + kBatch);
+        if constexpr (!DENSE) { if (probe_pending) probe(); }      // (behind the loads just issued)
+        if (first) {
+            if (base != vec_begin) pad_batch(buf_a, base);
+            stream_batch(buf_a, base, 0);
+        }
+        load_batch(buf_a, base + 2 * kBatch);
+        if (second) {
+            pad_batch(buf_b, base + kBatch);
+            stream_batch(buf_b, base + kBatch, UNROLL);
+        }
+        // Vectors to take up again, and room for the next pair of batches or the end of the slice.  No barrier at the end: a
+        // wave that is done streaming scores its queue against the bound as the workgroup knows it now, while slower waves
+        // still stream -- a few more entries are scored than with the final bound, but the scoring overlaps with the stream.
+        const int limit = last ? 0 : kRingV / 2;
+        if constexpr (!DENSE) { if (last) tighten(); }
+        bool compacted = false;
+        int todo = overflow | redo;
+        auto reload = [&](int bits) __attribute__((always_inline)) -> uint4 {            // vector of the lowest bit
+            const int vi = base + __builtin_ctz((unsigned)bits) * THREADS + tid;
+            return vi < full_end ? *(const uint4*)(rowp + (int64_t)vi * 16) : make_uint4(kPadWord, kPadWord, kPadWord, kPadWord);
+        };
+        uint4 ahead = todo ? reload(todo) : make_uint4(0u, 0u, 0u, 0u);                  // one vector ahead of its scoring
+        overflow = 0;
+        while (q_count > limit || todo) {
+            float x[EPV];
+            uint32_t vi;
+            bool in;
+            if (todo) {
+                const int u = __builtin_ctz((unsigned)todo);
+                vi = (uint32_t)(base + u * THREADS + tid);
+                in = (int)vi < full_end;
+                unpack<DT>(ahead, x);
+                todo &= todo - 1;
+                if (todo) ahead = reload(todo);
+                if (redo >> u & 1) {
+                    float d[EPV], e[EPV];
+                    relative(x, d);
+                    add_s1(d, e);
+                    add_sb(x, d, e);
+                }
+                redo &= ~(1 << u);
+            } else {
+                if (last) { publish(); adopt(); }
+                if (q_count > kWave && (last || !compacted)) { compact(); compacted = true; }
+                const int n = min(q_count, kWave);       // up to 64 queued vectors, one per lane
+                wave_sync();                             // ring writes of other lanes, same wave
+                in = lane < n;
+                const int slot = (q_head + lane) & (kRingV - 1);
+                unpack<DT>(in ? ring_raw[slot] : make_uint4(kPadWord, kPadWord, kPadWord, kPadWord), x);
+                vi = in ? ring_idx[slot] : 0u;
+                q_head = (q_head + n) & (kRingV - 1);
+                q_count -= n;
+            }
+            if constexpr (DENSE) { if (in) score_vector(x, vi, -INFINITY); }
+            else score_vectors(x, vi, in);
+        }
+        if constexpr (!DENSE) { if (last && e_count > 0) score_entries(e_count); }
+        if (last) break;
     }
 
     if constexpr (kDirect) {
@@ -857,20 +925,26 @@ __global__ __launch_bounds__(NW * kWave, 4) void vocab_pass_kernel(const StepArg
     }
     Partial* const slot_out = n_split > 1 ? a.partials + (int64_t)row * kMaxSplit + split : nullptr;
     block_epilogue<NW>(beta, m, M1, Mb, s1, sb, top, n_scored, n_drains, slot_out, &sh_part);
-    if (wave != 0) return;
+    }
 
     // ---- tail: the wave that completes the row finalizes it ---------------------------------------------------
-    const Partial* pp = &sh_part;
-    if (n_split > 1) {
-        const int tk = take_ticket(&a.row_ticket[row]);    // this slice's record (written by lane 0) is complete
-        if (tk != n_split - 1) return;
-        if (lane == 0) store_shared(&a.row_ticket[row], 0);    // nobody else touches it until the next step
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup"); // (keeps the reads of the records behind the ticket)
-        pp = a.partials + (int64_t)row * kMaxSplit;
+    if (wave != 0) return;
+    if (terminated) {
+        if (split != 0) return;
+        if (lane == 0) finalize_done_row(a, sc, row);
     } else {
-        wave_sync();                                   // lane 0's copy of the record in LDS
+        const Partial* pp = &sh_part;
+        if (n_split > 1) {
+            const int tk = take_ticket(&a.row_ticket[row]);    // this slice's record (written by lane 0) is complete
+            if (tk != n_split - 1) return;
+            if (lane == 0) store_shared(&a.row_ticket[row], 0);    // nobody else touches it until the next step
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup"); // (keeps the reads of the records behind the ticket)
+            pp = a.partials + (int64_t)row * kMaxSplit;
+        } else {
+            wave_sync();                                   // lane 0's copy of the record in LDS
+        }
+        finalize_row(a, sc, row, pp, n_split, row_state);
     }
-    finalize_row(a, sc, row, pp, n_split, row_state);
     after_row_final(a, sc, row, lds);
 }
 
