@@ -109,7 +109,8 @@ smc_status smc_step(smc_ctx* ctx, const void* d_logits, int64_t row_stride_elems
 /* a0 .. a4 in one call: smc_step followed by smc_resample, with the same arguments, outputs and results as the two
  * calls.  With fewer than 1024 rows it is ONE launch: the workgroup that completes a row finalizes it, and the wave
  * that finalizes the last row of a prompt goes on to normalise and resample that prompt, so no second launch (and no
- * launch gap) is needed.  Larger batches, where a launch is cheap beside the logit stream, take the two launches.
+ * launch gap) is needed.  Larger batches, where a launch is cheap beside the logit stream, and contexts tuned to four
+ * waves per workgroup take the two launches.
  * Follow it with smc_kv_reindex / smc_paged_reindex on d_anc_out / d_resampled_out as after smc_resample. */
 smc_status smc_step_resample(smc_ctx* ctx, const void* d_logits, int64_t row_stride_elems, int32_t t, double alpha_t,
                              double alpha_prev, double tau_t, int32_t* d_tokens_out, int32_t* d_anc_out,
@@ -117,9 +118,8 @@ smc_status smc_step_resample(smc_ctx* ctx, const void* d_logits, int64_t row_str
 
 /* a0 .. a5 in one call: smc_step_resample followed by smc_kv_reindex(d_anc_out, d_resampled_out, valid_len, t), with
  * the same arguments, outputs, results and errors as the two calls -- the whole per-token step of Alg. 1 ("sample",
- * "update", "resample", "reorder KV cache by A") in three launches at every size: with 1024 rows or more, where
- * smc_step_resample takes a launch of its own for the resampling, the wave that resamples a prompt goes on to plan
- * the prompt's reorder, so the plan needs no launch. */
+ * "update", "resample", "reorder KV cache by A") in two launches below 1024 rows and three above: what resamples a
+ * prompt goes on to plan the prompt's reorder, so the plan needs no launch of its own. */
 smc_status smc_step_resample_reindex(smc_ctx* ctx, const void* d_logits, int64_t row_stride_elems, int32_t t,
                                      double alpha_t, double alpha_prev, double tau_t, int32_t valid_len,
                                      int32_t* d_tokens_out, int32_t* d_anc_out, int32_t* d_resampled_out,

@@ -6,14 +6,6 @@
 
 namespace psmc {
 
-// Where a plan is written.
-struct PlanArgs {
-    int N, mask_words, skip_terminated;
-    GatherPlan* plan;
-    int32_t* grp_src; int32_t* grp_base; int32_t* grp_srcpar; unsigned long long* grp_mask;
-    double* cumlogp; int32_t* done; int32_t* parity;
-};
-
 // The plan of resampled prompt b by one team.  phase: which of the plan's two group counters this call uses.
 // The caller has filled and synchronised sh.anc (ancestors within the prompt; -1: the row is left untouched), sh.cum,
 // sh.done and sh.par (the rows' state before the reorder).

@@ -116,13 +116,15 @@ extern "C" smc_status smc_step_noalloc(const smc_config* cfg, void* hip_stream, 
     c.ws.d_rowstat = (int32_t*)(base + kOffRowstat);
     c.ws.row_ticket = (int32_t*)(base + kOffTicket);
     c.paged = PagedKV{};
-    auto_shape(c.R, cfg->V, cfg->logits_dtype, &c.wg_waves, &c.n_split);
+    auto_shape(c.R, cfg->V, cfg->logits_dtype, cfg->eos_id >= 0, &c.wg_waves, &c.n_split);
     c.mask_words = (cfg->N + 63) / 64;
     // The per-row ticket counters of the kernel must start at zero.  They return to zero by themselves, but the array is
     // shared by every call on this GPU, so it is cleared here rather than trusted (a fill kernel, not a memset node: the
-    // call may be under stream capture).
-    hipLaunchKernelGGL(clear_tickets_kernel, dim3((unsigned)((R + 255) / 256)), dim3(256), 0, c.stream, c.ws.row_ticket, (int)R);
-    if (hipGetLastError() != hipSuccess) return SMC_E_HIP;
+    // call may be under stream capture).  Rows of one slice take no tickets: 2048 bf16 rows 148 -> 143 us without the launch.
+    if (c.n_split > 1) {
+        hipLaunchKernelGGL(clear_tickets_kernel, dim3((unsigned)((R + 255) / 256)), dim3(256), 0, c.stream, c.ws.row_ticket, (int)R);
+        if (hipGetLastError() != hipSuccess) return SMC_E_HIP;
+    }
     return launch_vocab_pass(&c, d_logits, row_stride_elems, t, alpha_t, alpha_prev, tau_t, d_tokens_out, nullptr) == hipSuccess
                ? SMC_OK : SMC_E_HIP;
 }

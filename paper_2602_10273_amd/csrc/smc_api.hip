@@ -32,6 +32,29 @@ smc_status check_config(const smc_config* c)
     return SMC_OK;
 }
 
+// What smc_step and the calls that contain it check before anything is enqueued.
+smc_status check_step(const smc_ctx* ctx, const void* d_logits, int64_t row_stride_elems, int32_t t, double alpha_t,
+                      double alpha_prev, double tau_t, const int32_t* d_tokens_out)
+{
+    if (!ctx || !d_logits || !d_tokens_out) return SMC_E_NULL;
+    const int esz = ctx->cfg.logits_dtype == SMC_BF16 ? 2 : 4;
+    if (row_stride_elems < ctx->cfg.V) return SMC_E_SHAPE;
+    if (!aligned16(d_logits) || (row_stride_elems * esz) % 16 != 0) return SMC_E_ALIGN;
+    if (t < 1 || t > ctx->cfg.T_max) return SMC_E_RANGE;
+    if (!(alpha_t > 0.0) || !(alpha_prev >= 0.0) || !isfinite(alpha_t) || !isfinite(alpha_prev)) return SMC_E_RANGE;
+    if (!isfinite(tau_t)) return SMC_E_RANGE;
+    const double beta = tau_t <= 0.0 ? alpha_t : 1.0 / tau_t;
+    if (!(beta > 0.0) || !isfinite(beta) || beta > 1.0e4) return SMC_E_RANGE;
+    return SMC_OK;
+}
+
+// Folding the resampling into the vocabulary pass saves a launch, but the wave that resamples a prompt keeps its workgroup's
+// slot occupied while it does so.  With few rows the slot has nothing else to run and the fold is a gain; with a thousand rows or
+// more it delays the logit stream of the next row by more than the launch costs (measured on 2048 fp32 rows: 206 us folded
+// against 197 + 5 us apart), so large batches take the two launches.  So do the four-wave workgroups a caller may have asked
+// for at any size: they are the large batches' and carry no LDS for it.
+bool resamples_in_step(const smc_ctx* ctx) { return ctx->R < 1024 && ctx->wg_waves > 4; }
+
 // Walks the workspace layout; with base == nullptr only the size is computed.
 size_t layout(const smc_config* c, char* base, Workspace* w)
 {
@@ -74,19 +97,30 @@ namespace psmc {
 
 smc_status validate_config(const smc_config* c) { return check_config(c); }
 
-// Launch shape of the vocabulary pass.  Few rows: big workgroups (16 waves share their bound through LDS) and just
-// enough slices per row to put about one workgroup on each of the 256 CUs.  Many rows: 4-wave workgroups, one per row.
-void auto_shape(int R, int V, int dtype, int* wg_waves, int* n_split)
+// Launch shape of the vocabulary pass, by what was measured (us a step, V = 152064 bf16 unless noted).
+//   >= 1024 rows: a 4-wave workgroup per row.
+//   > 256 rows: an 8-wave workgroup per row, two of which fit a compute unit (384 rows: 50.0 against 55.5 with 16 waves;
+//     512 fp32 rows: 66.5 / 75.1; 768 rows: 75.9 / 88.8, and 78.6 with 4 waves).
+//   else 256 / rows slices per row: a 16-wave workgroup fills a compute unit.  Rounded down, because one workgroup more than
+//     there are units is a second round (200 rows: 33.2 with one slice, 45.1 with two); but up where an end-of-sequence
+//     token is configured, because the rows that have terminated are not read and leave room (120 rows of 50257, 90 of them
+//     terminated: 29.6 with three slices, 35.3 with two).
+//     16 waves while they have more than 2 vectors a thread to stream (64 rows: 22.7 against 24.0 with 8 waves; 128 rows:
+//     26.8 / 30.9), 8 for shorter slices, where every further wave only repeats the start, the bound and the merge
+//     (8 rows: 16.6 against 18.4; 32 fp32 rows of 32000: 15.1 / 17.3; 128 rows of 32000: 17.0 / 18.6).
+void auto_shape(int R, int V, int dtype, bool rows_terminate, int* wg_waves, int* n_split)
 {
+    constexpr int kUnits = 256;                        // compute units
     const int epv = dtype == SMC_BF16 ? 8 : 4;
-    const int nvec = (V + epv - 1) / epv;
-    if (R >= 1024) { *wg_waves = 4; *n_split = 1; return; }
-    *wg_waves = 16;
-    const int tiles = (nvec + 1023) / 1024;
-    int s = (256 + R - 1) / R;
-    if (s > tiles) s = tiles;
+    const int64_t nvec = ((int64_t)V + epv - 1) / epv;
+    *n_split = 1;
+    if (R >= 1024) { *wg_waves = 4; return; }
+    if (R > kUnits) { *wg_waves = 8; return; }
+    int s = rows_terminate ? (kUnits + R - 1) / R : kUnits / R;
     if (s > kMaxSplit) s = kMaxSplit;
-    if (s < 1) s = 1;
+    *wg_waves = nvec > (int64_t)2 * 16 * kWave * s ? 16 : 8;
+    const int64_t tiles = (nvec + *wg_waves * kWave - 1) / (*wg_waves * kWave);
+    if (s > tiles) s = (int)tiles;
     *n_split = s;
 }
 
@@ -131,7 +165,7 @@ smc_status smc_init(const smc_config* cfg, void* d_workspace, size_t workspace_b
     c->stream = (hipStream_t)hip_stream;
     c->R = cfg->B * cfg->N;
     layout(cfg, (char*)d_workspace, &c->ws);
-    auto_shape(c->R, cfg->V, cfg->logits_dtype, &c->wg_waves, &c->n_split);
+    auto_shape(c->R, cfg->V, cfg->logits_dtype, cfg->eos_id >= 0, &c->wg_waves, &c->n_split);
     c->dense = 0;
     c->mask_words = (cfg->N + 63) / 64;
     c->resampler = 0;
@@ -215,15 +249,8 @@ smc_status smc_kv_parity(smc_ctx* ctx, const int32_t** d_parity)
 smc_status smc_step(smc_ctx* ctx, const void* d_logits, int64_t row_stride_elems, int32_t t, double alpha_t,
                     double alpha_prev, double tau_t, int32_t* d_tokens_out)
 {
-    if (!ctx || !d_logits || !d_tokens_out) return SMC_E_NULL;
-    const int esz = ctx->cfg.logits_dtype == SMC_BF16 ? 2 : 4;
-    if (row_stride_elems < ctx->cfg.V) return SMC_E_SHAPE;
-    if (!aligned16(d_logits) || (row_stride_elems * esz) % 16 != 0) return SMC_E_ALIGN;
-    if (t < 1 || t > ctx->cfg.T_max) return SMC_E_RANGE;
-    if (!(alpha_t > 0.0) || !(alpha_prev >= 0.0) || !isfinite(alpha_t) || !isfinite(alpha_prev)) return SMC_E_RANGE;
-    if (!isfinite(tau_t)) return SMC_E_RANGE;
-    const double beta = tau_t <= 0.0 ? alpha_t : 1.0 / tau_t;
-    if (!(beta > 0.0) || !isfinite(beta) || beta > 1.0e4) return SMC_E_RANGE;
+    const smc_status st = check_step(ctx, d_logits, row_stride_elems, t, alpha_t, alpha_prev, tau_t, d_tokens_out);
+    if (st != SMC_OK) return st;
     return launch_vocab_pass(ctx, d_logits, row_stride_elems, t, alpha_t, alpha_prev, tau_t, d_tokens_out, nullptr) == hipSuccess
                ? SMC_OK : SMC_E_HIP;
 }
@@ -232,25 +259,15 @@ smc_status smc_step_resample(smc_ctx* ctx, const void* d_logits, int64_t row_str
                              double alpha_prev, double tau_t, int32_t* d_tokens_out, int32_t* d_anc_out,
                              int32_t* d_resampled_out, double* d_ess_out)
 {
-    if (!ctx || !d_logits || !d_tokens_out || !d_anc_out || !d_resampled_out) return SMC_E_NULL;
-    const int esz = ctx->cfg.logits_dtype == SMC_BF16 ? 2 : 4;
-    if (row_stride_elems < ctx->cfg.V) return SMC_E_SHAPE;
-    if (!aligned16(d_logits) || (row_stride_elems * esz) % 16 != 0) return SMC_E_ALIGN;
-    if (t < 1 || t > ctx->cfg.T_max) return SMC_E_RANGE;
-    if (!(alpha_t > 0.0) || !(alpha_prev >= 0.0) || !isfinite(alpha_t) || !isfinite(alpha_prev)) return SMC_E_RANGE;
-    if (!isfinite(tau_t)) return SMC_E_RANGE;
-    const double beta = tau_t <= 0.0 ? alpha_t : 1.0 / tau_t;
-    if (!(beta > 0.0) || !isfinite(beta) || beta > 1.0e4) return SMC_E_RANGE;
-    // Folding the resampling into the launch saves a launch, but the wave that resamples a prompt keeps its workgroup's
-    // slot occupied while it does so.  With few rows the slot has nothing else to run and the fold is a gain; with a
-    // thousand rows or more it delays the logit stream of the next row by more than the launch costs (measured on 2048
-    // fp32 rows: 206 us folded against 197 + 5 us apart), so large batches take the two launches.
-    if (ctx->R >= 1024) {
+    if (!ctx || !d_anc_out || !d_resampled_out) return SMC_E_NULL;
+    const smc_status st = check_step(ctx, d_logits, row_stride_elems, t, alpha_t, alpha_prev, tau_t, d_tokens_out);
+    if (st != SMC_OK) return st;
+    if (!resamples_in_step(ctx)) {
         if (launch_vocab_pass(ctx, d_logits, row_stride_elems, t, alpha_t, alpha_prev, tau_t, d_tokens_out, nullptr) != hipSuccess)
             return SMC_E_HIP;
         return launch_resample(ctx, ctx->ws.logW, t, d_anc_out, d_resampled_out, d_ess_out) == hipSuccess ? SMC_OK : SMC_E_HIP;
     }
-    const FusedResample f{d_anc_out, d_resampled_out, d_ess_out};
+    const FusedResample f{d_anc_out, d_resampled_out, d_ess_out, false};
     return launch_vocab_pass(ctx, d_logits, row_stride_elems, t, alpha_t, alpha_prev, tau_t, d_tokens_out, &f) == hipSuccess
                ? SMC_OK : SMC_E_HIP;
 }
@@ -297,18 +314,20 @@ smc_status smc_step_resample_reindex(smc_ctx* ctx, const void* d_logits, int64_t
     if (!ctx) return SMC_E_NULL;
     if (valid_len < 0 || (ctx->cfg.kv_tensors > 0 && valid_len > ctx->cfg.kv_S)) return SMC_E_RANGE;
     if (ctx->cfg.kv_tensors > 0 && valid_len > 0 && !ctx->kv_bound) return SMC_E_STATE;
-    if (ctx->R < 1024) {
-        // few rows: the resampling already rides in the vocabulary pass's launch; plan and gather follow
-        const smc_status st = smc_step_resample(ctx, d_logits, row_stride_elems, t, alpha_t, alpha_prev, tau_t, d_tokens_out,
-                                                d_anc_out, d_resampled_out, d_ess_out);
-        if (st != SMC_OK) return st;
-        return launch_reindex(ctx, d_anc_out, d_resampled_out, valid_len, t) == hipSuccess ? SMC_OK : SMC_E_HIP;
-    }
-    // many rows: the vocabulary pass, then one launch that resamples every prompt and plans its reorder, then the gather
     if (!d_anc_out || !d_resampled_out) return SMC_E_NULL;
-    const smc_status st = smc_step(ctx, d_logits, row_stride_elems, t, alpha_t, alpha_prev, tau_t, d_tokens_out);
+    const smc_status st = check_step(ctx, d_logits, row_stride_elems, t, alpha_t, alpha_prev, tau_t, d_tokens_out);
     if (st != SMC_OK) return st;
-    if (launch_resample_plan(ctx, ctx->ws.logW, t, d_anc_out, d_resampled_out, d_ess_out) != hipSuccess) return SMC_E_HIP;
+    if (resamples_in_step(ctx)) {
+        // few rows: resampling and plan ride in the vocabulary pass's launch; the gather follows
+        const FusedResample f{d_anc_out, d_resampled_out, d_ess_out, true};
+        if (launch_vocab_pass(ctx, d_logits, row_stride_elems, t, alpha_t, alpha_prev, tau_t, d_tokens_out, &f) != hipSuccess)
+            return SMC_E_HIP;
+    } else {
+        // many rows: the vocabulary pass, then one launch that resamples every prompt and plans its reorder, then the gather
+        if (launch_vocab_pass(ctx, d_logits, row_stride_elems, t, alpha_t, alpha_prev, tau_t, d_tokens_out, nullptr) != hipSuccess)
+            return SMC_E_HIP;
+        if (launch_resample_plan(ctx, ctx->ws.logW, t, d_anc_out, d_resampled_out, d_ess_out) != hipSuccess) return SMC_E_HIP;
+    }
     return launch_reindex(ctx, d_anc_out, d_resampled_out, valid_len, t, true) == hipSuccess ? SMC_OK : SMC_E_HIP;
 }
 
@@ -508,7 +527,7 @@ smc_status smc_set_tuning(smc_ctx* ctx, int32_t n_split, int32_t dense, int32_t 
     if (wg_waves != 0 && wg_waves != 4 && wg_waves != 8 && wg_waves != 16) return SMC_E_RANGE;
     if (dense < 0 || dense > 1) return SMC_E_RANGE;
     int aw, as;
-    auto_shape(ctx->R, ctx->cfg.V, ctx->cfg.logits_dtype, &aw, &as);
+    auto_shape(ctx->R, ctx->cfg.V, ctx->cfg.logits_dtype, ctx->cfg.eos_id >= 0, &aw, &as);
     ctx->wg_waves = wg_waves == 0 ? aw : wg_waves;
     ctx->n_split = n_split == 0 ? (wg_waves == 0 || wg_waves == aw ? as : 1) : n_split;
     ctx->dense = dense;

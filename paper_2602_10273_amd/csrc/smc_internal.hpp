@@ -43,7 +43,7 @@ struct GatherPlan {
 // What one wave needs to normalise and resample one prompt (a3 + a4).
 struct ResampleArgs {
     int N;
-    double kappa;
+    double kappa, log_N;
     uint32_t key0, key1;
     int scheme, order;
     int32_t* anc;                 // [R] out: ancestors as global row indices
@@ -52,8 +52,16 @@ struct ResampleArgs {
     double* logZhat;              // [B] in/out, nullable: running log of the normalising-constant estimate
 };
 
-// Outputs of a resampling folded into the vocabulary-pass launch.
-struct FusedResample { int32_t* anc; int32_t* resampled; double* ess_out; };
+// Outputs of a resampling folded into the vocabulary-pass launch; plan: the reorder of the same call is planned as well.
+struct FusedResample { int32_t* anc; int32_t* resampled; double* ess_out; bool plan; };
+
+// Where the plan of a reorder is written.
+struct PlanArgs {
+    int N, mask_words, skip_terminated;
+    GatherPlan* plan;
+    int32_t* grp_src; int32_t* grp_base; int32_t* grp_srcpar; unsigned long long* grp_mask;
+    double* cumlogp; int32_t* done; int32_t* parity;
+};
 
 // Everything the vocabulary-pass kernel and its tail (row finalizer, optional resampling) take.
 struct StepArgs {
@@ -70,10 +78,12 @@ struct StepArgs {
     double* logW; double* cumlogp; const int32_t* parity; int32_t* const* histAB; int T_max; int32_t* tokens_out;
     double* d_delta; double* d_logZ1; double* d_logZb; double* d_gap; int32_t* d_second; int32_t* d_rowstat;
     int eos_id; int32_t* done;
-    // resampling folded into the same launch
-    int fuse_resample;
+    // resampling, and the plan of the reorder that follows, folded into the same launch
+    int fuse_resample, fuse_plan;
+    int n_prompts;
     int32_t* prompt_ticket;       // [B] rows of a prompt that are final (returns to 0)
     ResampleArgs rs;
+    PlanArgs pl;
 };
 
 struct Workspace {                // device pointers carved out of the caller's workspace
@@ -177,11 +187,12 @@ struct ScopedKernelTimer {
 smc_status validate_config(const smc_config* c);
 
 // default launch shape of the vocabulary pass for R rows of V entries: waves per workgroup and workgroups per row
-void auto_shape(int R, int V, int dtype, int* wg_waves, int* n_split);
+void auto_shape(int R, int V, int dtype, bool rows_terminate, int* wg_waves, int* n_split);
 
 // launchers (each enqueues on ctx->stream; returns hipGetLastError())
 hipError_t launch_init_state(smc_ctx* c);
-// fused: not null -> the wave that completes a prompt also resamples it (a3 + a4 in the same launch)
+// fused: not null -> the wave that completes a prompt also resamples it (a3 + a4 in the same launch); needs more than
+// four waves per workgroup
 hipError_t launch_vocab_pass(smc_ctx* c, const void* logits, int64_t row_stride, int t, double alpha_t,
                              double alpha_prev, double tau_t, int32_t* tokens_out, const FusedResample* fused);
 hipError_t launch_advance_step(smc_ctx* c);

@@ -7,6 +7,7 @@ namespace psmc {
 
 hipError_t launch_vocab_bf16(smc_ctx* c, const StepArgs& a, int P);    // vocab_pass_bf16.hip
 hipError_t launch_vocab_f32(smc_ctx* c, const StepArgs& a, int P);     // vocab_pass_f32.hip
+PlanArgs plan_args(const smc_ctx* c);                                  // kv_gather.hip
 
 // Advances the context's device-resident step counter (one thread).
 __global__ void advance_step_kernel(int32_t* d_step) { if (threadIdx.x == 0 && blockIdx.x == 0) *d_step += 1; }
@@ -58,11 +59,12 @@ hipError_t launch_vocab_pass(smc_ctx* c, const void* logits, int64_t row_stride,
         a.d_step = w.d_step; a.d_sched = w.d_sched; a.n_sched = c->n_sched;
         P = tau_t <= 0.0 ? c->sched_integer_power : integer_power(a.beta);
     }
-    a.fuse_resample = 0;
     if (fused) {
         a.fuse_resample = 1;
+        a.n_prompts = c->cfg.B;
         a.prompt_ticket = w.prompt_ticket;
         a.rs = resample_args(c, w.logW, fused->anc, fused->resampled, fused->ess_out);
+        if (fused->plan) { a.fuse_plan = 1; a.pl = plan_args(c); }
     }
 
     ScopedKernelTimer timer(c, 0);

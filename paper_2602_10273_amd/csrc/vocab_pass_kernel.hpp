@@ -26,11 +26,13 @@
 // Tail.  The workgroup that writes the last slice of a row (a ticket per row) merges the row's slices in fp64,
 // re-ranks the finalists with fp64 keys, and applies the boundary reweight and the increment.  With resampling
 // folded in, the wave that finalizes the last row of a prompt (a ticket per prompt) goes on to normalise the
-// prompt's weights and resample it.  Tickets return to zero by themselves, so the launch can be replayed.  What is handed
+// prompt's weights, resample it and, where the reorder follows in the same call, plan it.  (A ticket costs 0.5 us.
+// Finalizing all rows of a prompt side by side behind a single ticket was slower by 2 to 7 us: rows that are final early
+// no longer overlap with the stream of the others.)  Tickets return to zero by themselves, so the launch can be replayed.  What is handed
 // over behind a ticket (a slice's record, a row's weight) is written and read at agent scope, and the ticket is taken once
 // those writes have completed; no cache is written back or invalidated for it.
 #pragma once
-#include "weights_device.hpp"
+#include "gather_plan_device.hpp"
 
 namespace psmc {
 
@@ -399,8 +401,8 @@ __device__ inline void finalize_row(const StepArgs& a, const StepScalars& sc, ui
         const double delta = alpha_t * logp - logq;
         double w = rs.logW + (alpha_t - alpha_prev) * rs.cumlogp;          // stage boundary on the prefix y_{1:t-1}
         w += delta;
-        store_shared(&a.logW[row], w);                  // (the wave that resamples the prompt may belong to another workgroup)
-        a.cumlogp[row] = rs.cumlogp + logp;
+        store_shared(&a.logW[row], w);                  // (the wave that resamples and plans the prompt may belong to another workgroup)
+        store_shared(&a.cumlogp[row], rs.cumlogp + logp);
         a.tokens_out[row] = tok;
         // (a device-resident step may have run past the end of the history)
         if (rs.hist && step >= 1u && step <= (uint32_t)a.T_max) rs.hist[(int64_t)row * a.T_max + (step - 1)] = tok;
@@ -408,7 +410,7 @@ __device__ inline void finalize_row(const StepArgs& a, const StepScalars& sc, ui
         a.d_gap[row] = gap;
         a.d_second[row] = second;
         a.d_rowstat[3 * row] = ok ? 0 : 1; a.d_rowstat[3 * row + 1] = nsc; a.d_rowstat[3 * row + 2] = ndr;
-        if (a.eos_id >= 0 && ok && tok == a.eos_id) a.done[row] = 1;
+        if (a.eos_id >= 0 && ok && tok == a.eos_id) store_shared(&a.done[row], 1);
     }
 }
 
@@ -426,23 +428,36 @@ __device__ inline void finalize_done_row(const StepArgs& a, const StepScalars& s
     a.d_rowstat[3 * row] = 0; a.d_rowstat[3 * row + 1] = 0; a.d_rowstat[3 * row + 2] = 0;
 }
 
-// After a row is final: with resampling folded into this launch, the wave that completes a prompt resamples it.
-// lds: PromptLds::weight_bytes(N), free for this wave's use.
+// After a row is final: with resampling folded into this launch, the wave that completes a prompt resamples it and, on
+// request, plans its reorder.  lds: PromptLds::plan_bytes(N), free for this wave's use.
 __device__ inline void after_row_final(const StepArgs& a, const StepScalars& sc, uint32_t row, unsigned char* lds)
 {
     if (!a.fuse_resample) return;
     const int N = a.rs.N;
     const int b = (int)row / N;
+    const int64_t row0 = (int64_t)b * N;
     const int tk = take_ticket(&a.prompt_ticket[b]);   // this row's weight has been written
     if (tk != N - 1) return;
     const Team tm{lane_id(), kWave};
     if (tm.tid == 0) store_shared(&a.prompt_ticket[b], 0);   // nobody else touches it until the next step
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup"); // (keeps the reads below behind the ticket)
     const PromptLds sh(lds, N);
-    // at agent scope: other workgroups may have written these weights a moment ago
-    for (int i = tm.tid; i < N; i += tm.n) sh.w[i] = load_shared(a.logW + (int64_t)b * N + i);
+    const int phase = a.fuse_plan ? a.pl.plan->phase : 0;
+    // at agent scope: other workgroups may have written these a moment ago
+    for (int i = tm.tid; i < N; i += tm.n) {
+        sh.w[i] = load_shared(a.logW + row0 + i);
+        if (a.fuse_plan) {
+            sh.cum[i] = load_shared(a.cumlogp + row0 + i);
+            sh.done[i] = load_shared(a.done + row0 + i);
+            sh.par[i] = a.parity[row0 + i];
+        }
+    }
     tm.sync();
-    resample_prompt(a.rs, a.logW + (int64_t)b * N, b, sc.step, tm, sh);
+    const bool fire = resample_prompt(a.rs, a.logW + row0, b, sc.step, tm, sh);
+    if (a.fuse_plan) {
+        if (fire) plan_prompt(a.pl, b, phase, tm, sh);
+        plan_finish(a.pl.plan, phase, a.n_prompts);
+    }
 }
 
 }  // namespace
@@ -471,9 +486,11 @@ __global__ __launch_bounds__(NW * kWave, 4) void vocab_pass_kernel(const StepArg
     constexpr int kScoreAsVectors = 160;
     constexpr int kRingE = 256;                        // queued single entries per wave: what one drain adds to less than a wave-width
     static_assert(kScoreAsVectors + kWave <= kRingE, "a drain's entries must fit");
-    // LDS: the candidate rings while streaming; afterwards the same bytes serve the resampling of a prompt
-    constexpr int kRingBytes = DENSE ? 0 : NW * (kRingV * 20 + kRingE * 8);
-    constexpr int kTailBytes = (int)PromptLds::weight_bytes(SMC_MAX_PARTICLES);
+    // LDS: the candidate rings while streaming; afterwards the same bytes serve the resampling of a prompt (which the small
+    // workgroups of large batches never do: their LDS decides how many rows a compute unit streams at a time)
+    constexpr bool kMayResample = NW > 4;
+    constexpr int kRingBytes = DENSE ? 16 : NW * (kRingV * 20 + kRingE * 8);
+    constexpr int kTailBytes = kMayResample ? (int)PromptLds::plan_bytes(SMC_MAX_PARTICLES) : 16;
     constexpr int kLdsBytes = kRingBytes > kTailBytes ? kRingBytes : kTailBytes;
     __shared__ __align__(16) unsigned char lds[kLdsBytes];
     __shared__ int wg_bound;                           // best "cannot win below this" bound of the whole workgroup
@@ -945,7 +962,7 @@ __global__ __launch_bounds__(NW * kWave, 4) void vocab_pass_kernel(const StepArg
         }
         finalize_row(a, sc, row, pp, n_split, row_state);
     }
-    after_row_final(a, sc, row, lds);
+    if constexpr (kMayResample) after_row_final(a, sc, row, lds);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -3,6 +3,8 @@
 //
 // The sums that decide discrete outcomes (ESS < kappa*N, cumulative weights against the resampling positions)
 // are accumulated in particle order by one lane, so that they round like a plain left-to-right loop.
+#include <math.h>
+
 #include "gather_plan_device.hpp"
 #include "weights_device.hpp"
 
@@ -153,7 +155,7 @@ hipError_t launch_ess(smc_ctx* c, const double* logW, double* ess_out, double* l
 ResampleArgs resample_args(const smc_ctx* c, double* logW, int32_t* anc, int32_t* resampled, double* ess_out)
 {
     ResampleArgs r;
-    r.N = c->cfg.N; r.kappa = c->cfg.kappa;
+    r.N = c->cfg.N; r.kappa = c->cfg.kappa; r.log_N = log((double)c->cfg.N);
     r.key0 = (uint32_t)c->cfg.seed; r.key1 = (uint32_t)(c->cfg.seed >> 32);
     r.scheme = c->resampler; r.order = c->ancestor_order;
     r.anc = anc; r.resampled = resampled; r.ess_out = ess_out;

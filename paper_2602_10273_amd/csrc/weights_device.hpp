@@ -142,7 +142,8 @@ __device__ inline void serial_scan(const double* a, double* c, int N)
 }
 
 // log-sum-exp of x_i and of 2 x_i over one prompt, particle order, from sh.w (written and synchronised by the caller).
-// Returns on every thread of the team.
+// Returns on every thread of the team.  One copy of the exponential and one of the logarithm, with the terms side by side on
+// the lanes: a short launch waits for its code (fp64 exp and log take about 100 instructions each).
 __device__ inline void prompt_lse(const Team& tm, int N, const PromptLds& sh, double& L1, double& L2)
 {
     double mx = -INFINITY;
@@ -154,15 +155,12 @@ __device__ inline void prompt_lse(const Team& tm, int N, const PromptLds& sh, do
         for (int k = 0; k < tm.n / kWave; ++k) mx = fmax(mx, sh.red[k]);
     }
     const int Np = pad_serial(N);
-    for (int i = tm.tid; i < Np; i += tm.n) {
-        double ea = 0.0, eb = 0.0;
-        if (i < N) {
-            const double w = sh.w[i];
-            ea = exp(w - mx);
-            eb = exp(2.0 * w - 2.0 * mx);
-        }
-        sh.a[i] = ea;
-        sh.b[i] = eb;
+#pragma unroll 1
+    for (int k = tm.tid; k < 2 * Np; k += tm.n) {      // sh.a, then sh.b, which follows it
+        const int i = k < Np ? k : k - Np;
+        const double w = i < N ? sh.w[i] : 0.0;
+        const double x = exp(k < Np ? w - mx : 2.0 * w - 2.0 * mx);
+        sh.a[k] = i < N ? x : 0.0;
     }
     tm.sync();
     double s1 = 0.0, s2 = 0.0;
@@ -172,8 +170,9 @@ __device__ inline void prompt_lse(const Team& tm, int N, const PromptLds& sh, do
         __syncthreads();
         s1 = sh.red[16]; s2 = sh.red[17];
     }
-    L1 = mx + log(s1);
-    L2 = 2.0 * mx + log(s2);
+    const double lg = log((tm.tid & 1) ? s2 : s1);
+    L1 = mx + read_lane(lg, 0);
+    L2 = 2.0 * mx + read_lane(lg, 1);
     tm.sync();                                          // sh.a and sh.b are free again
 }
 
@@ -276,22 +275,29 @@ __device__ inline bool resample_prompt(const ResampleArgs& r, double* __restrict
     const int N = r.N;
     double L1, L2;
     prompt_lse(tm, N, sh, L1, L2);
-    const double ess = exp(2.0 * L1 - L2);
+    // the normalised weights, wanted only if the prompt resamples, and the ESS in one more pass through the exponential
+    const int Np = pad_serial(N);
+    double ess = 0.0;
+#pragma unroll 1
+    for (int i = tm.tid; i < Np + 1; i += tm.n) {
+        const double x = exp(i < N ? sh.w[i] - L1 : 2.0 * L1 - L2);
+        if (i < Np) sh.a[i] = i < N ? x : 0.0;
+        else sh.red[18] = x;
+    }
+    tm.sync();
+    ess = sh.red[18];
     const bool fire = ess < r.kappa * (double)N;         // strict; false for NaN
     if (tm.tid == 0) {
         if (r.ess_out) r.ess_out[b] = ess;
         r.resampled[b] = fire ? 1 : 0;
         // running estimate of the normalising constant: every resampling contributes the mean unnormalised weight
-        if (fire && r.logZhat) r.logZhat[b] += L1 - log((double)N);
+        if (fire && r.logZhat) r.logZhat[b] += L1 - r.log_N;
     }
     int32_t* A = r.anc + (int64_t)b * N;
     if (!fire) {
         for (int i = tm.tid; i < N; i += tm.n) A[i] = b * N + i;
         return false;
     }
-    const int Np = pad_serial(N);
-    for (int i = tm.tid; i < Np; i += tm.n) sh.a[i] = i < N ? exp(sh.w[i] - L1) : 0.0;
-    tm.sync();
     if (r.scheme == 3) {
         residual_ancestors(r, b, step, tm, sh);
     } else {
