@@ -82,11 +82,14 @@ __device__ inline void load_plan_state(const PlanArgs& pl, int b, const Team& tm
 // The two group counters alternate between successive plans, and the switch happens on the device: every workgroup
 // of a plan reads plan->phase first and calls this last; the one with the last ticket clears the other counter for
 // the next plan and flips the phase.  No host-side state is involved, so a captured launch sequence can be replayed.
+// (The read of the phase has to precede the ticket, and it has: its value chose the counter that was added to.  A device-wide
+// fence here would write back and invalidate caches for nothing.)
 __device__ inline void plan_finish(GatherPlan* plan, int phase, int n_workgroups)
 {
     if (threadIdx.x == 0) {
-        __threadfence();                                           // the read of plan->phase precedes the ticket
-        if (atomicAdd(&plan->ticket, 1) == n_workgroups - 1) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);                        // vmcnt(0): the phase has arrived
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");     // (for the compiler's order)
+        if (__hip_atomic_fetch_add(&plan->ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_workgroups - 1) {
             plan->n_groups[phase ^ 1] = 0;
             plan->ticket = 0;
             plan->phase = phase ^ 1;

@@ -33,6 +33,15 @@ static_assert(kEntriesPerBlock >= SMC_MAX_PARTICLES, "one column of a prompt mus
 constexpr int kScanPerThread = 32;                  // reference counts one thread examines per sweep of the free-page search
 typedef unsigned int vec16 __attribute__((ext_vector_type(4)));
 
+// Waits until this thread's memory operations have been carried out (loads arrived, stores and atomics acknowledged): all a
+// workgroup needs between what it wrote itself and its own reads behind a barrier, or between its reads and a ticket.  A
+// device-wide fence would write back and invalidate caches as well.
+__device__ __forceinline__ void wait_memory()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0)
+}
+
 // Exclusive prefix sum of one int per thread over the 256-thread workgroup; `total` is the sum over all threads.
 __device__ inline int block_exclusive_scan(int v, int32_t* sh_wave, int& total)
 {
@@ -140,13 +149,15 @@ __global__ __launch_bounds__(kPagedThreads) void paged_reorder_kernel(
                 for (int v = lo + tid; v < hi; v += kPagedThreads) *(vec16*)(dst + (long long)v * 16) = *(const vec16*)(src + (long long)v * 16);
             }
         }
+        wait_memory();
         __syncthreads();
-        if (tid == 0) {
-            __threadfence();                                   // this workgroup's reads precede its ticket
-            sh_last = atomicAdd(&arrive[b], 1) == hb - 1;
+        // the ticket is taken once this workgroup's reads have been answered (and copied from); a prompt of one state
+        // workgroup needs none
+        if (hb > 1) {
+            if (tid == 0) sh_last = atomicAdd(&arrive[b], 1) == hb - 1;
+            __syncthreads();
         }
-        __syncthreads();
-        if (sh_last) {
+        if (hb == 1 || sh_last) {
             for (int k = tid; k < N; k += kPagedThreads) {
                 const int a = sh_anc[k];
                 if (a >= 0) {
@@ -155,7 +166,7 @@ __global__ __launch_bounds__(kPagedThreads) void paged_reorder_kernel(
                     parity[row0 + k] = sh_aux[k] ^ 1;
                 }
             }
-            if (tid == 0) arrive[b] = 0;
+            if (tid == 0 && hb > 1) arrive[b] = 0;
         }
         return;
     }
@@ -193,6 +204,15 @@ __global__ __launch_bounds__(kPagedThreads) void paged_reorder_kernel(
         }
     }
     if (prepare) {
+        if (chunks == 1) {
+            // the prompt is this workgroup's alone: its own entries and counts have to be out, no other's.  (The counts were
+            // changed by atomics beyond the first-level cache, which may hold their line: another prompt's shares it.)
+            wait_memory();
+            __syncthreads();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            prepare_prompt(b, B, N, M, Q, pa, table, refcnt);
+            return;
+        }
         // every thread's table entries and counts are out before the workgroup's ticket; the workgroup with the
         // prompt's last ticket sees what the others wrote
         __threadfence();
@@ -299,7 +319,7 @@ __device__ void prepare_prompt(int b, int n_prompts, int N, int M, int Q, const 
         slot[row0 + k] = page;
     }
     if (tid == 0) {
-        __threadfence();                               // the read of counters[3] precedes the ticket
+        wait_memory();                                 // the read of counters[3] precedes the ticket
         if (atomicAdd(&counters[4], 1) == n_prompts - 1) {
             counters[phase ^ 1] = 0;
             counters[4] = 0;

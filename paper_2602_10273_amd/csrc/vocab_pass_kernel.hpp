@@ -470,8 +470,9 @@ __device__ inline void after_row_final(const StepArgs& a, const StepScalars& sc,
 // instructions (134 KB, twice the instruction cache; now 47 KB), and a launch over few rows spent its time fetching them.
 // Measured (bf16, V = 152064, beta = 4 unless noted): 64 rows 26.8 -> 22.5 us, 128 rows 29.4 -> 26.7, 256 rows at beta = 6
 // 34.0 -> 28.3, 2048 rows 147 -> 141 (VALU-bound: 8066 vector instructions a wave, of which the 74 vectors of its stream
-// take 62 each, scoring 1400 and start and end 760); 2048 fp32 rows unchanged at 6.2 TB/s.  Summing on the matrix cores
-// (v_mfma_f32_4x4x1, one entry per lane) instead of the vector ALUs was slower (182 us for 2048 rows).
+// take 62 each, scoring 1400 and start and end 760); 2048 fp32 rows unchanged at 6.2 TB/s.  Then, with the vectors of a
+// slice's last batch that hold nothing but padding passed over: 64 rows 21.7, 128 rows 26.1, 2048 rows 136 to 138.  Summing
+// on the matrix cores (v_mfma_f32_4x4x1, one entry per lane) instead of the vector ALUs was slower (182 us for 2048 rows).
 template <int DT, int P, bool DENSE, int NW>
 __global__ __launch_bounds__(NW * kWave, 4) void vocab_pass_kernel(const StepArgs a)
 {
@@ -811,6 +812,8 @@ __global__ __launch_bounds__(NW * kWave, 4) void vocab_pass_kernel(const StepArg
         float dm[UNROLL];
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
+            dm[u] = -INFINITY;
+            if (b0 + u * THREADS + wave * kWave >= full_end) continue;     // (scalar) nothing but padding in the wave's vector
             const int vi = b0 + u * THREADS + tid;
             float x[EPV], d[EPV], e[EPV];
             unpack<DT>(src[u], x);
