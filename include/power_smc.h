@@ -156,8 +156,8 @@ smc_status smc_get_device_step(smc_ctx* ctx, int32_t* h_t);
  *   d_done_inout: device int32 [R] termination flags, read and updated; required when eos_id >= 0, else ignored.
  * No token history is written.  Calls nothing that allocates (no hipMalloc / hipFree, no workspace); argument errors
  * are detected on the host before anything is enqueued.  Every call on one GPU uses that GPU's one scratch array,
- * which keeps the previous call's contents (only the per-row ticket counters have to start at zero; each call clears
- * them with a small fill kernel first, everything else it reads it has written itself): calls that overlap in time
+ * which keeps the previous call's contents (only the per-row ticket counters have to start at zero; a call that splits
+ * its rows over several workgroups clears them with a small fill kernel first, everything else it reads it has written itself): calls that overlap in time
  * on one GPU -- other streams, other threads -- race on it and must be serialised by the caller. */
 smc_status smc_step_noalloc(const smc_config* cfg, void* hip_stream, const void* d_logits, int64_t row_stride_elems,
                             int32_t t, double alpha_t, double alpha_prev, double tau_t, double* d_logW_inout,

@@ -8,8 +8,8 @@
 // The array exists once per GPU (each device that loads the library holds its own copy until the process ends).
 // Its device address is looked up once per device with hipGetSymbolAddress and kept; host code never passes the
 // array's name to a kernel.  Every call on a GPU uses that GPU's one array: calls that overlap in time on one GPU
-// (different streams, or different threads) race on it.  Only the per-row ticket counters have to start at zero; each call
-// clears them first.  Every record that the finalizer reads is written by the vocabulary pass of the same call.
+// (different streams, or different threads) race on it.  Only the per-row ticket counters have to start at zero; a call
+// that splits rows clears them first (a row that one workgroup streams takes no ticket).  Every record that the finalizer reads is written by the vocabulary pass of the same call.
 #include <math.h>
 
 #include <mutex>

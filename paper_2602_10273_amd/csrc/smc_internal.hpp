@@ -139,7 +139,7 @@ struct smc_ctx {
     int R;
     int n_split;                  // current split of a row over workgroups
     int dense;                    // 1: score every vocabulary entry (no candidate filter)
-    int wg_waves;                 // waves per workgroup of the vocabulary pass: 4 or 16
+    int wg_waves;                 // waves per workgroup of the vocabulary pass: 4, 8 or 16
     int mask_words;               // 64-bit words per descendant bit set = ceil(N/64)
     int resampler;                // 0 systematic (the paper's), 1 stratified, 2 multinomial, 3 residual
     int ancestor_order;           // 0 as drawn, 1 survivors stay in place
